@@ -116,7 +116,7 @@ Layout layout(const dp_geom& g, int V, int op)
         break;
     case DP_OP_FP_BP_GRAD:
         L.chunk = det_chunk(g, V, sizeof(float4), V);
-        off = align_up(off + (size_t)L.chunk * padded_image_elems(g) * sizeof(float4));
+        off = align_up(off + (size_t)L.chunk * g.nu * g.nv * sizeof(float2));
         L.n_part = (size_t)sf_blocks(s);
         L.partials = off;
         off = align_up(off + (size_t)V * L.n_part * kVdChannels * sizeof(float));
@@ -499,15 +499,15 @@ int dp_fp_backproject_grad_pose(const dp_geom* g, int32_t V, const double* angle
     hipStream_t st = (hipStream_t)stream;
     char* base = (char*)ws;
     ViewGeo* views = (ViewGeo*)(base + L.views);
-    float4* proj4 = (float4*)(base + L.buf);
+    float2* grad_img = (float2*)(base + L.buf);
     float* part = (float*)(base + L.partials);
     (void)hipGetLastError();
     launch_view_setup(s, V, angles, poses, views, st);
     const size_t img = (size_t)g->nu * g->nv;
     for (int v0 = 0; v0 < V; v0 += L.chunk) {
         const int vc = std::min(L.chunk, V - v0);
-        launch_det_grad(s, vc, proj + v0 * img, proj4, st);
-        launch_sf_bp_grad(s, v0, vc, views, proj4, grad_vol, part, kind, st);
+        launch_det_grad(s, vc, proj + v0 * img, grad_img, st);
+        launch_sf_bp_grad(s, v0, vc, views, grad_img, grad_vol, part, kind, st);
     }
     launch_finalize_bp(s, V, views, part, (int)L.n_part, grad_pose, st);
     return check_launch("dp_fp_backproject_grad_pose");

@@ -106,7 +106,7 @@ void launch_view_setup(const GeoScalars& s, int V, const double* angles, const d
                        ViewGeo* views, hipStream_t st);
 // per padded pixel, the bilinear cell coefficients of l as one float4
 void launch_det_pad(const GeoScalars& s, int V, const float* proj, float4* projq, hipStream_t st);
-void launch_det_grad(const GeoScalars& s, int V, const float* proj, float4* proj4, hipStream_t st);
+void launch_det_grad(const GeoScalars& s, int V, const float* proj, float2* grad, hipStream_t st);
 void launch_det_tap3(const GeoScalars& s, int V, const float* proj, DetTap3* det, hipStream_t st);
 // The ray-driven kernels read the caller's volume [nz][ny][nx] directly.
 void launch_rd_fwd(const GeoScalars& s, int V, const ViewGeo* views, const float* mu,
@@ -228,9 +228,9 @@ void launch_sf_bp(const GeoScalars& s, int V, const ViewGeo* views, const float*
                   int kind, hipStream_t st);
 void launch_sf_fwd_grad(const GeoScalars& s, int V, const ViewGeo* views, const float* vol,
                         const float* grad_proj, float* partials, int kind, hipStream_t st);
-// views [v0, v0 + Vc), proj4 = this chunk's detector gradient images
+// views [v0, v0 + Vc), grad_img = this chunk's detector gradient images
 void launch_sf_bp_grad(const GeoScalars& s, int v0, int Vc, const ViewGeo* views,
-                       const float4* proj4, const float* grad_vol, float* partials, int kind,
+                       const float2* grad_img, const float* grad_vol, float* partials, int kind,
                        hipStream_t st);
 
 // FDK pre-filter and sharpness loss (fdk.hip).

@@ -4,8 +4,8 @@
 //     zero-extended image on the cell to its lower right as one float4, for
 //     the back-projection;
 //   - detector gradient field (central differences of l, Sec. II-C) stored
-//     as float4 (l, dl/da, dl/db, 0) in pixel-index units, zero outside
-//     (footprint projectors), or as the cell coefficients of the three fields
+//     as (dl/da, dl/db) per pixel in pixel-index units (footprint
+//     projectors), or as the cell coefficients of l and both derivatives
 //     (voxel-driven back-projection gradient).
 // Cell coefficients of pixel (A, B): with v_xy the image at (A + x, B + y),
 //   (v00, v10 - v00, v01 - v00, v11 - v10 - v01 + v00),
@@ -43,22 +43,17 @@ __global__ __launch_bounds__(256) void det_pad_kernel(int nu, int nv, const floa
                   pix_at(img, nu, nv, a, b + 1), pix_at(img, nu, nv, a + 1, b + 1));
 }
 
+// (dl/da, dl/db) per pixel: the footprint projectors' gradient image.
 __global__ __launch_bounds__(256) void det_grad_kernel(int nu, int nv, const float* __restrict__ proj,
-                                                       float4* __restrict__ proj4)
+                                                       float2* __restrict__ grad)
 {
-    const int NU = nu + 2 * kPadD, NV = nv + 2 * kPadD;
-    const int A = blockIdx.x * blockDim.x + threadIdx.x;
-    const int B = blockIdx.y, v = blockIdx.z;
-    if (A >= NU) return;
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    const int b = blockIdx.y, v = blockIdx.z;
+    if (a >= nu) return;
     const float* img = proj + (size_t)v * nu * nv;
-    const int a = A - kPadD, b = B - kPadD;
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a >= 0 && b >= 0 && a < nu && b < nv) {
-        o.x = img[(size_t)b * nu + a];
-        o.y = 0.5f * (pix_at(img, nu, nv, a + 1, b) - pix_at(img, nu, nv, a - 1, b));
-        o.z = 0.5f * (pix_at(img, nu, nv, a, b + 1) - pix_at(img, nu, nv, a, b - 1));
-    }
-    proj4[((size_t)v * NV + B) * NU + A] = o;
+    grad[((size_t)v * nv + b) * nu + a] =
+        make_float2(0.5f * (pix_at(img, nu, nv, a + 1, b) - pix_at(img, nu, nv, a - 1, b)),
+                    0.5f * (pix_at(img, nu, nv, a, b + 1) - pix_at(img, nu, nv, a, b - 1)));
 }
 
 // l, dl/da, dl/db at pixel (a, b) of the zero-extended image (derivatives:
@@ -160,12 +155,11 @@ void launch_det_pad(const GeoScalars& s, int V, const float* proj, float4* projq
     prof_end(DP_K_DET_PREP, st);
 }
 
-void launch_det_grad(const GeoScalars& s, int V, const float* proj, float4* proj4, hipStream_t st)
+void launch_det_grad(const GeoScalars& s, int V, const float* proj, float2* grad, hipStream_t st)
 {
-    const int NU = s.nu + 2 * kPadD;
-    dim3 grid((NU + 255) / 256, s.nv + 2 * kPadD, V);
+    dim3 grid((s.nu + 255) / 256, s.nv, V);
     prof_begin(DP_K_DET_PREP, st);
-    det_grad_kernel<<<grid, 256, 0, st>>>(s.nu, s.nv, proj, proj4);
+    det_grad_kernel<<<grid, 256, 0, st>>>(s.nu, s.nv, proj, grad);
     prof_end(DP_K_DET_PREP, st);
 }
 

@@ -62,18 +62,18 @@ constexpr double kSfPixClamp = 1048576.0;  // projections beyond 2^20 pixels are
 // Integral of the unit-height trapezoid over [x0, x1] (relative to abase),
 // segment by segment: rising edge (x - t0) / (t1 - t0), plateau, falling
 // edge (t3 - x) / (t3 - t2).  Each term is a product of short differences,
-// so no digits are lost when breakpoints lie far from the cell.
+// so no digits are lost when breakpoints lie far from the cell; an edge the
+// cell does not reach (or a vertical one) contributes exactly zero.
+template <int KIND>
 __device__ inline float trap_integral(float x0, float x1, const SfFootprint& f)
 {
     const float* t = f.tau;
     float s = fmaxf(fminf(x1, t[2]) - fmaxf(x0, t[1]), 0.0f);
-    if (t[1] > t[0]) {
-        const float l = fmaxf(x0, t[0]), r = fminf(x1, t[1]);
-        if (r > l) s += (r - l) * ((r - t[0]) + (l - t[0])) * f.r01;
-    }
-    if (t[3] > t[2]) {
-        const float l = fmaxf(x0, t[2]), r = fminf(x1, t[3]);
-        if (r > l) s += (r - l) * ((t[3] - l) + (t[3] - r)) * f.r23;
+    if (KIND == kFpSF) {
+        const float l0 = fmaxf(x0, t[0]), r0 = fminf(x1, t[1]);
+        s += fmaxf(r0 - l0, 0.0f) * ((r0 - t[0]) + (l0 - t[0])) * f.r01;
+        const float l1 = fmaxf(x0, t[2]), r1 = fminf(x1, t[3]);
+        s += fmaxf(r1 - l1, 0.0f) * ((t[3] - l1) + (t[3] - r1)) * f.r23;
     }
     return s;
 }
@@ -82,6 +82,26 @@ __device__ inline float row_overlap(float b, float lo, float hi)
 {
     const float o = fminf(b + 0.5f, hi) - fmaxf(b - 0.5f, lo);
     return o > 0.0f ? o : 0.0f;
+}
+
+// Slope factor of an edge from lo to hi, 1 / (2 (hi - lo)), to ~1 ulp (hardware
+// rcp: only relative precision is needed).  An edge narrower than 1e-30 pixels
+// counts as vertical, so the factor is finite.
+__device__ inline float sf_slope(float lo, float hi)
+{
+    return hi - lo > 1.0e-30f ? 0.5f * __builtin_amdgcn_rcpf(hi - lo) : 0.0f;
+}
+
+// Slopes and pixel window of a footprint whose breakpoints, rows and bases are
+// set (the bases and relative offsets are bounded, so no overflow).
+__device__ inline void sf_window(const GeoScalars& s, SfFootprint& f)
+{
+    f.r01 = sf_slope(f.tau[0], f.tau[1]);
+    f.r23 = sf_slope(f.tau[2], f.tau[3]);
+    f.a0 = max(f.abase + (int)floorf(f.tau[0] - 0.5f) + 1, 0);
+    f.a1 = min(f.abase + (int)ceilf(f.tau[3] + 0.5f) - 1, s.nu - 1);
+    f.b0 = max(f.bbase + (int)floorf(f.blo - 0.5f) + 1, 0);
+    f.b1 = min(f.bbase + (int)ceilf(f.bhi + 0.5f) - 1, s.nv - 1);
 }
 
 // The parts every producer shares: sort (SF), slopes, amplitude, window.
@@ -107,10 +127,6 @@ __device__ inline void sf_finish(const GeoScalars& s, int dom, float* t, const f
         t[2] = t[3] = hi;
     }
     for (int c = 0; c < 4; ++c) f.tau[c] = t[c];
-    // reciprocals to ~1 ulp (hardware rcp): every quantity here needs only
-    // relative precision
-    f.r01 = t[1] > t[0] ? 0.5f * __builtin_amdgcn_rcpf(t[1] - t[0]) : 0.0f;
-    f.r23 = t[3] > t[2] ? 0.5f * __builtin_amdgcn_rcpf(t[3] - t[2]) : 0.0f;
     f.blo = fminf(bb[0], bb[1]);
     f.bhi = fmaxf(bb[0], bb[1]);
     // amplitude: SF the chord min_a h_a |d| / |d_a|, DD the slab path
@@ -129,11 +145,7 @@ __device__ inline void sf_finish(const GeoScalars& s, int dom, float* t, const f
     f.L = L;
     f.abase = abase;
     f.bbase = bbase;
-    // window (the bases and relative offsets are bounded, so no overflow)
-    f.a0 = max(abase + (int)floorf(t[0] - 0.5f) + 1, 0);
-    f.a1 = min(abase + (int)ceilf(t[3] + 0.5f) - 1, s.nu - 1);
-    f.b0 = max(bbase + (int)floorf(f.blo - 0.5f) + 1, 0);
-    f.b1 = min(bbase + (int)ceilf(f.bhi + 0.5f) - 1, s.nv - 1);
+    sf_window(s, f);
 }
 
 // Column breakpoint line q of voxel column (i, j): SF corner (i +- 1/2,
@@ -200,6 +212,7 @@ __device__ inline bool sf_footprint(const ViewGeo& g, const GeoScalars& s, const
 // and only the small offset dk N / W(dk) is evaluated per voxel, in FP32.
 struct SfColumn {
     bool fast;       // false: an anchor within 1 mm of the source plane (per-voxel FP64)
+    bool front;      // fast, and every line stays in front of the source along the column
     int abase, bbase;
     float tfr[4], tn[4], tw[4];  // breakpoint lines: anchor offset from abase, N, W0
     float bfr, bn, bw;           // centre line: row offset from bbase, N_v, W0
@@ -207,6 +220,7 @@ struct SfColumn {
     float uco, bco;              // abase - c_u, bbase - c_v (offsets from the detector centre)
     float pwz, ka;
     float d0, d1, d2o;           // source-to-voxel line: x, y (mm) and z offset
+    float i0, i1;                // 1 / |d0|, 1 / |d1|
 };
 
 template <int KIND>
@@ -214,7 +228,7 @@ __device__ inline SfColumn sf_column(const ViewGeo& g, const GeoScalars& s, cons
                                      int dom, int i, int j, int ka)
 {
     SfColumn c;
-    c.fast = false;
+    c.fast = c.front = false;
     const double fi = i, fj = j, fk = ka;
     constexpr int NL = KIND == kFpSF ? 4 : 2;
     double A[NL];
@@ -254,7 +268,16 @@ __device__ inline SfColumn sf_column(const ViewGeo& g, const GeoScalars& s, cons
     c.d0 = (float)((fi - src[0]) * s.vx);
     c.d1 = (float)((fj - src[1]) * s.vy);
     c.d2o = (float)(-src[2] * s.vz);
+    c.i0 = __builtin_amdgcn_rcpf(fabsf(c.d0));
+    c.i1 = __builtin_amdgcn_rcpf(fabsf(c.d1));
     c.fast = true;
+    // depths are linear along the column: positive at both ends, positive between
+    const float e0 = -0.5f * kSfCol - 0.5f, e1 = 0.5f * kSfCol - 0.5f;
+    float wmin = fminf(fmaf(e0, c.pwz, c.bw), fmaf(e1, c.pwz, c.bw));
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+        wmin = fminf(wmin, fminf(fmaf(e0, c.pwz, c.tw[q]), fmaf(e1, c.pwz, c.tw[q])));
+    c.front = wmin > 0.0f;
     return c;
 }
 
@@ -286,6 +309,83 @@ __device__ inline bool sf_voxel(const SfColumn& c, const ViewGeo& g, const GeoSc
     return true;
 }
 
+// Projected row (relative to bbase) of the column's centre line at dk voxels
+// from the anchor; a front column only.
+__device__ inline float sf_row(const SfColumn& c, float dk)
+{
+    return fmaf(dk * c.bn, __builtin_amdgcn_rcpf(fmaf(dk, c.pwz, c.bw)), c.bfr);
+}
+
+// Correctly rounded square root of a normal x up to rare last bits, in half
+// the instructions of sqrtf (no scaling of denormals).
+__device__ inline float sf_sqrt(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x), r = x * y;
+    return fmaf(fmaf(-r, r, x), 0.5f * y, r);
+}
+
+// Footprint of voxel k of a front column, without its pixel window: no depth
+// tests, and the row bound shared with the voxel below (row_lo, updated to the
+// bound shared with the next one).
+template <int KIND>
+struct SfBox {
+    float t[4];      // breakpoints in order (DD: t[0] = t[1], t[2] = t[3])
+    float blo, bhi;  // row rectangle
+    float L;         // amplitude
+};
+
+template <int KIND>
+__device__ inline SfBox<KIND> sf_box(const SfColumn& c, const GeoScalars& s, int dom, int k,
+                                     float& row_lo)
+{
+    constexpr int NL = KIND == kFpSF ? 4 : 2;
+    SfBox<KIND> f;
+    const float dk = (float)k - c.ka;
+    float t[NL];
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+        t[q] = fmaf(dk * c.tn[q], __builtin_amdgcn_rcpf(fmaf(dk, c.pwz, c.tw[q])), c.tfr[q]);
+    const float h0 = (float)s.vx, h1 = (float)s.vy, h2 = (float)s.vz;
+    const float d2 = fmaf((float)k, h2, c.d2o);
+    const float n = sf_sqrt(c.d0 * c.d0 + c.d1 * c.d1 + d2 * d2);
+    if constexpr (KIND == kFpSF) {
+        const float l0 = fminf(t[0], t[1]), g0 = fmaxf(t[0], t[1]);
+        const float l1 = fminf(t[2], t[3]), g1 = fmaxf(t[2], t[3]);
+        f.t[0] = fminf(l0, l1);
+        f.t[3] = fmaxf(g0, g1);
+        const float m0 = fmaxf(l0, l1), m1 = fminf(g0, g1);
+        f.t[1] = fminf(m0, m1);
+        f.t[2] = fmaxf(m0, m1);
+        // an axis the line does not move along has 1 / |d| = inf and drops out
+        f.L = fminf(fminf(h0 * n * c.i0, h1 * n * c.i1),
+                    h2 * n * __builtin_amdgcn_rcpf(fabsf(d2)));
+    } else {
+        f.t[0] = f.t[1] = fminf(t[0], t[1]);
+        f.t[2] = f.t[3] = fmaxf(t[0], t[1]);
+        const float hd = dom == 0 ? h0 : h1, dd = dom == 0 ? c.d0 : c.d1, id = dom == 0 ? c.i0 : c.i1;
+        f.L = dd != 0.0f ? hd * n * id : 0.0f;
+    }
+    const float up = sf_row(c, dk + 0.5f);
+    f.blo = fminf(row_lo, up);
+    f.bhi = fmaxf(row_lo, up);
+    row_lo = up;
+    return f;
+}
+
+// The same voxel with its slopes and window, for the general pixel loops.
+template <int KIND>
+__device__ inline void sf_unbox(const SfBox<KIND>& x, const SfColumn& c, const GeoScalars& s,
+                                SfFootprint& f)
+{
+    for (int q = 0; q < 4; ++q) f.tau[q] = x.t[q];
+    f.blo = x.blo;
+    f.bhi = x.bhi;
+    f.L = x.L;
+    f.abase = c.abase;
+    f.bbase = c.bbase;
+    sf_window(s, f);
+}
+
 // Source position in object-frame (unpadded) voxel-index units, and the
 // view's dominant transaxial axis for DD (0 = x, 1 = y).
 __device__ inline int sf_source(const ViewGeo& g, const GeoScalars& s, double* src)
@@ -300,12 +400,12 @@ __device__ inline int sf_source(const ViewGeo& g, const GeoScalars& s, double* s
 // the window with a non-zero weight w = column integral x row overlap
 // (without the amplitude L); the column integral is evaluated once per
 // column.
-template <typename Fn>
+template <int KIND, typename Fn>
 __device__ inline void sf_for_each(const SfFootprint& f, Fn&& fn)
 {
     for (int a = f.a0; a <= f.a1; ++a) {
         const float x = (float)(a - f.abase);
-        const float wa = trap_integral(x - 0.5f, x + 0.5f, f);
+        const float wa = trap_integral<KIND>(x - 0.5f, x + 0.5f, f);
         if (wa == 0.0f) continue;
         for (int b = f.b0; b <= f.b1; ++b) {
             const float wb = row_overlap((float)(b - f.bbase), f.blo, f.bhi);
@@ -314,12 +414,239 @@ __device__ inline void sf_for_each(const SfFootprint& f, Fn&& fn)
     }
 }
 
-// Gather sum_i a_ij img_i over the footprint (img: [nv][nu]).
-__device__ inline float sf_gather(const SfFootprint& f, const float* __restrict__ img, int nu)
+// ---------------------------------------------------------------------------
+// Gathers.  Bound by VALU issue, not by the loads: a voxel's window is read as
+// a patch of up to 4 columns and 3 rows (nearly every footprint: a voxel
+// magnified to about two pixels), one unaligned 16-byte load per row and
+// channel, and every weight of the patch is formed without branches from
+// cell edges clamped to the footprint's segments (each edge serves both its
+// cells; cells outside get exactly zero).  Columns 2, 3 and row 2 are skipped
+// when no lane of the wavefront has them.  Wavefronts with larger windows
+// take their pixels in several such quads of up to 5 rows, and lanes beyond
+// that, or whose sum is not finite (a pixel of weight zero may hold
+// anything), pixel by pixel.  All of these add the same products in the same
+// order (columns outside, rows inside).
+// Measured from a 256^3 volume of 0.8 mm voxels and 384^2 views of 0.8 mm
+// pixels, against loops over each lane's own window in an unrolled column:
+// DD back-projection of 64 views 9.88 -> 3.79 ms (2.8e11 voxel-view updates/s,
+// about 110 VALU instructions each beside the FP64 column anchors) and its
+// gradient 5.40 -> 2.18 ms; SF forward gradient of 4 views 0.78 -> 0.30 ms.
+// Four blocks per CU; five or six spill and are slower (1.03x, 1.4x).
+// ---------------------------------------------------------------------------
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) const f32x4u sf_global4;
+typedef __attribute__((address_space(1))) const char sf_bytes;
+
+__device__ inline bool sf_any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
+
+// floor(x) as an integer in one instruction (saturating; 0 for NaN).
+__device__ inline int sf_floor(float x)
 {
-    float acc = 0.0f;
-    sf_for_each(f, [&](int a, int b, float w) { acc = fmaf(w, img[(size_t)b * nu + a], acc); });
-    return f.L * acc;
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// A detector image [nv][nu] (at most 16384 x 16384: 32-bit byte offsets from a
+// wave-uniform base).
+struct SfImage {
+    static constexpr int C = 1;
+    const float* img;
+    int nu;
+    __device__ inline void row4(int a, int b, float (&v)[1][4]) const
+    {
+        const unsigned o = (unsigned)(__mul24(b, 4 * nu) + 4 * a);
+        const f32x4u q = *(sf_global4*)((sf_bytes*)img + o);
+        v[0][0] = q.x; v[0][1] = q.y; v[0][2] = q.z; v[0][3] = q.w;
+    }
+    __device__ inline void pixel(int a, int b, float (&v)[1]) const { v[0] = img[(unsigned)(b * nu + a)]; }
+};
+
+// A detector gradient image: (dl/da, dl/db) per pixel, [nv][nu].
+struct SfGradImage {
+    static constexpr int C = 2;
+    const float2* img;
+    int nu;
+    __device__ inline void row4(int a, int b, float (&v)[2][4]) const
+    {
+        const unsigned o = (unsigned)(__mul24(b, 8 * nu) + 8 * a);
+        const f32x4u q = *(sf_global4*)((sf_bytes*)img + o), r = *(sf_global4*)((sf_bytes*)img + 16 + o);
+        v[0][0] = q.x; v[1][0] = q.y; v[0][1] = q.z; v[1][1] = q.w;
+        v[0][2] = r.x; v[1][2] = r.y; v[0][3] = r.z; v[1][3] = r.w;
+    }
+    __device__ inline void pixel(int a, int b, float (&v)[2]) const
+    {
+        const float2 q = img[(unsigned)(b * nu + a)];
+        v[0] = q.x; v[1] = q.y;
+    }
+};
+
+// Adds the pixels of the window's columns a .. a + 3 (a >= 0, nu >= 4) and
+// first 5 rows.  The loads start at most at column nu - 4; columns before a
+// are left out.
+template <int KIND, class Img>
+__device__ inline void sf_quad(const SfFootprint& f, const GeoScalars& s, const Img& img, int a,
+                               float (&acc)[Img::C])
+{
+    constexpr int NR = 5;
+    const int s0 = min(a, s.nu - 4);
+    const float x = (float)(s0 - f.abase);
+    float v[NR][Img::C][4], wb[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        img.row4(s0, min(f.b0 + r, s.nv - 1), v[r]);
+        wb[r] = f.b0 + r <= f.b1 ? row_overlap((float)(f.b0 + r - f.bbase), f.blo, f.bhi) : 0.0f;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const float wa = s0 + t >= a ? trap_integral<KIND>(x + (float)t - 0.5f, x + (float)t + 0.5f, f)
+                                     : 0.0f;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int c = 0; c < Img::C; ++c) acc[c] = fmaf(wa * wb[r], v[r][c][t], acc[c]);
+    }
+}
+
+// acc = sum_i a_ij img_i over the footprint, any window.
+template <int KIND, class Img>
+__device__ inline void sf_gather(const SfFootprint& f, const GeoScalars& s, const Img& img,
+                                 float (&acc)[Img::C])
+{
+#pragma unroll
+    for (int c = 0; c < Img::C; ++c) acc[c] = 0.0f;
+    bool loop = s.nu < 4 || f.b1 - f.b0 >= 5;
+    if (!loop && f.b0 <= f.b1)
+        for (int a = f.a0; a <= f.a1; a += 4) sf_quad<KIND>(f, s, img, a, acc);
+#pragma unroll
+    for (int c = 0; c < Img::C; ++c) loop = loop || !(fabsf(acc[c]) < INFINITY);
+    if (loop) {
+#pragma unroll
+        for (int c = 0; c < Img::C; ++c) acc[c] = 0.0f;
+        sf_for_each<KIND>(f, [&](int a, int b, float w) {
+            float v[Img::C];
+            img.pixel(a, b, v);
+#pragma unroll
+            for (int c = 0; c < Img::C; ++c) acc[c] = fmaf(w, v[c], acc[c]);
+        });
+    }
+#pragma unroll
+    for (int c = 0; c < Img::C; ++c) acc[c] *= f.L;
+}
+
+// Weights of N cells from edge e on (cells [e, e + 1], ...): column integrals
+// of the trapezoid, row overlaps.
+template <int KIND, int N>
+__device__ inline void sf_cells(const float (&t)[4], float e, float (&w)[N])
+{
+    if constexpr (KIND == kFpSF) {
+        const float r01 = sf_slope(t[0], t[1]), r23 = sf_slope(t[2], t[3]);
+        float p = __builtin_amdgcn_fmed3f(e, t[1], t[2]);
+        float u = __builtin_amdgcn_fmed3f(e, t[0], t[1]), du = u - t[0];
+        float d = __builtin_amdgcn_fmed3f(e, t[2], t[3]), dd = t[3] - d;
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const float x = e + (float)(q + 1);
+            const float p1 = __builtin_amdgcn_fmed3f(x, t[1], t[2]);
+            const float u1 = __builtin_amdgcn_fmed3f(x, t[0], t[1]), du1 = u1 - t[0];
+            const float d1 = __builtin_amdgcn_fmed3f(x, t[2], t[3]), dd1 = t[3] - d1;
+            w[q] = fmaf((d1 - d) * (dd + dd1), r23, fmaf((u1 - u) * (du1 + du), r01, p1 - p));
+            p = p1; u = u1; du = du1; d = d1; dd = dd1;
+        }
+    } else {
+        float p = __builtin_amdgcn_fmed3f(e, t[0], t[3]);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const float p1 = __builtin_amdgcn_fmed3f(e + (float)(q + 1), t[0], t[3]);
+            w[q] = p1 - p;
+            p = p1;
+        }
+    }
+}
+
+// The gather of a front column's voxel (nu >= 4).
+template <int KIND, class Img>
+__device__ inline void sf_gather_box(const SfBox<KIND>& x, const SfColumn& c, const GeoScalars& s,
+                                     const Img& img, float (&acc)[Img::C])
+{
+    const int a0 = max(c.abase + sf_floor(x.t[0] - 0.5f) + 1, 0), s0 = min(a0, s.nu - 4);
+    const int b0 = max(c.bbase + sf_floor(x.blo - 0.5f) + 1, 0);
+    const float xs = (float)(s0 - c.abase), ys = (float)(b0 - c.bbase);
+    const float ta = x.t[3] + 0.5f, tb = x.bhi + 0.5f;
+    const bool fits = (ta <= xs + 4.0f || s0 + 4 >= s.nu) && (tb <= ys + 3.0f || b0 + 3 >= s.nv);
+    bool general = true;
+    if (!sf_any(!fits)) {
+        float v[3][Img::C][4], wa[4], wb[3];
+        const bool row2 = sf_any(tb > ys + 2.0f);
+        img.row4(s0, min(b0, s.nv - 1), v[0]);
+        img.row4(s0, min(b0 + 1, s.nv - 1), v[1]);
+        if (row2) img.row4(s0, min(b0 + 2, s.nv - 1), v[2]);
+        const float tr[4] = {x.blo, x.blo, x.bhi, x.bhi};
+        sf_cells<kFpDD, 3>(tr, ys - 0.5f, wb);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (b0 + r >= s.nv) wb[r] = 0.0f;
+        sf_cells<KIND, 4>(x.t, xs - 0.5f, wa);
+#pragma unroll
+        for (int q = 0; q < Img::C; ++q) acc[q] = 0.0f;
+        const auto add = [&](int t) {
+#pragma unroll
+            for (int q = 0; q < Img::C; ++q) {
+                acc[q] = fmaf(wa[t] * wb[0], v[0][q][t], acc[q]);
+                acc[q] = fmaf(wa[t] * wb[1], v[1][q][t], acc[q]);
+                if (row2) acc[q] = fmaf(wa[t] * wb[2], v[2][q][t], acc[q]);
+            }
+        };
+        add(0);
+        add(1);
+        if (sf_any(ta > xs + 2.0f)) add(2);
+        if (sf_any(ta > xs + 3.0f)) add(3);
+        general = false;
+#pragma unroll
+        for (int q = 0; q < Img::C; ++q) {
+            general = general || !(fabsf(acc[q]) < INFINITY);
+            acc[q] *= x.L;
+        }
+    }
+    if (general) {
+        SfFootprint f;
+        sf_unbox<KIND>(x, c, s, f);
+        sf_gather<KIND>(f, s, img, acc);
+    }
+}
+
+// Walks the nk voxels from kb on of a thread's column in one view, calling
+// fn(kk, k, acc) with the footprint-weighted image sums of every projected
+// voxel for which want(kk) holds.  Wavefronts whose columns all lie in front
+// of the source take the fast gather; the voxel loop stays rolled (one copy of
+// the code, and of its registers).
+template <int KIND, class Img, class Want, class Fn>
+__device__ inline void sf_walk(const SfColumn& col, const ViewGeo& g, const GeoScalars& s,
+                               const double* src, int dom, int i, int j, int kb, int nk,
+                               const Img& img, Want&& want, Fn&& fn)
+{
+    if (s.nu >= 4 && !sf_any(!col.front)) {
+        float row_lo = sf_row(col, (float)kb - col.ka - 0.5f);
+#pragma unroll 1
+        for (int kk = 0; kk < nk; ++kk) {
+            const SfBox<KIND> x = sf_box<KIND>(col, s, dom, kb + kk, row_lo);
+            if (!want(kk)) continue;
+            float acc[Img::C];
+            sf_gather_box<KIND>(x, col, s, img, acc);
+            fn(kk, kb + kk, acc);
+        }
+    } else {
+#pragma unroll 1
+        for (int kk = 0; kk < nk; ++kk) {
+            if (!want(kk)) continue;
+            SfFootprint f;
+            if (!sf_voxel<KIND>(col, g, s, src, dom, i, j, kb + kk, f)) continue;
+            float acc[Img::C];
+            sf_gather<KIND>(f, s, img, acc);
+            fn(kk, kb + kk, acc);
+        }
+    }
 }
 
 // Forward scatter.  A wavefront's 64 lanes take 64 neighbouring voxels
@@ -362,56 +689,78 @@ __global__ __launch_bounds__(kSfBx * kSfBy, 5) void sf_fwd_kernel(GeoScalars s, 
             SfFootprint f;
             if (!sf_voxel<KIND>(col, g, s, src, dom, i, j, k, f)) continue;
             const float scale = f.L * mu;
-            sf_for_each(f, [&](int a, int b, float w) {
+            sf_for_each<KIND>(f, [&](int a, int b, float w) {
                 atomicAdd(img + (size_t)b * s.nu + a, w * scale);
             });
         }
     }
 }
 
+
+// Back-projection: a thread owns kSfCol voxels along z, whose FP64 sums over
+// the views stay in LDS.
 template <int KIND>
 __global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_bp_kernel(GeoScalars s, int V,
                                                               const ViewGeo* __restrict__ views,
                                                               const float* __restrict__ proj,
                                                               float* __restrict__ vol)
 {
+    __shared__ double sum[kSfCol][kSfBx * kSfBy];
     const int i = blockIdx.x * kSfBx + threadIdx.x;
     const int j = blockIdx.y * kSfBy + threadIdx.y;
-    const int kb = blockIdx.z * kSfCol;
+    const int kb = blockIdx.z * kSfCol, nk = min(kSfCol, s.nz - kb);
+    const int tid = threadIdx.y * kSfBx + threadIdx.x;
     if (i >= s.nx || j >= s.ny) return;
-    double acc[kSfCol];
-#pragma unroll
-    for (int kk = 0; kk < kSfCol; ++kk) acc[kk] = 0.0;
+    for (int kk = 0; kk < kSfCol; ++kk) sum[kk][tid] = 0.0;
     for (int v = 0; v < V; ++v) {
         const ViewGeo& g = views[v];
         double src[3];
         const int dom = sf_source(g, s, src);
-        const float* img = proj + (size_t)v * s.nu * s.nv;
+        const SfImage img{proj + (size_t)v * s.nu * s.nv, s.nu};
         const SfColumn col = sf_column<KIND>(g, s, src, dom, i, j, kb + kSfCol / 2);
-#pragma unroll
-        for (int kk = 0; kk < kSfCol; ++kk) {
-            if (kb + kk >= s.nz) break;
-            SfFootprint f;
-            if (sf_voxel<KIND>(col, g, s, src, dom, i, j, kb + kk, f)) acc[kk] += sf_gather(f, img, s.nu);
-        }
+        sf_walk<KIND>(col, g, s, src, dom, i, j, kb, nk, img, [](int) { return true; },
+                      [&](int kk, int, const float (&acc)[1]) { sum[kk][tid] += acc[0]; });
     }
-#pragma unroll
-    for (int kk = 0; kk < kSfCol; ++kk)
-        if (kb + kk < s.nz) vol[((size_t)(kb + kk) * s.ny + j) * s.nx + i] = (float)acc[kk];
+    for (int kk = 0; kk < nk; ++kk) vol[((size_t)(kb + kk) * s.ny + j) * s.nx + i] = (float)sum[kk][tid];
 }
 
 // Per-view block reduction of C channels into partials[v][blk][C] (fixed
-// order: wavefront butterflies, then the 4 wavefronts in sequence).
-template <int C>
-__device__ inline void sf_reduce_store(float (&r)[C], float (&red)[kSfBy][C], float* out)
+// order: wavefront butterflies, then the 4 wavefronts in sequence).  At the
+// first butterfly steps each lane keeps half of its channels and receives the
+// partner's sums of them, so C channels take about C + log C exchanges
+// instead of 6 C; the additions are those of the full butterfly.
+template <int N>
+__device__ inline void sf_halve(float (&r)[N], float (&o)[(N + 1) / 2], bool high, int off)
 {
+    constexpr int H = (N + 1) / 2;
+#pragma unroll
+    for (int t = 0; t < H; ++t) {
+        const float up = H + t < N ? r[H + t] : 0.0f;
+        const float keep = high ? up : r[t], give = high ? r[t] : up;
+        o[t] = keep + __shfl_xor(give, off);
+    }
+}
+
+// The steps after the first: r1 holds the half of the C channels that the
+// lane kept (the first (C + 1) / 2 in lanes 0 .. 31).
+template <int C>
+__device__ inline void sf_reduce_half(float (&r1)[(C + 1) / 2], float (&red)[kSfBy][C], float* out)
+{
+    constexpr int C1 = (C + 1) / 2, C2 = (C1 + 1) / 2;
     const int lane = threadIdx.x, wave = threadIdx.y;
+    float r2[C2];
+    sf_halve(r1, r2, (lane & 16) != 0, 16);
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch)
-        for (int off = 32; off > 0; off >>= 1) r[ch] += __shfl_xor(r[ch], off);
-    if (lane == 0) {
+    for (int off = 8; off > 0; off >>= 1)
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch) red[wave][ch] = r[ch];
+        for (int t = 0; t < C2; ++t) r2[t] += __shfl_xor(r2[t], off);
+    if ((lane & 15) == 0) {
+        // lanes 0, 16, 32, 48 hold the channels from 0, C2, C1, C1 + C2 on
+        const int first = (lane & 32 ? C1 : 0) + (lane & 16 ? C2 : 0);
+        const int last = min(lane & 32 ? C : C1, (lane & 16) ? first + C1 : first + C2);
+#pragma unroll
+        for (int t = 0; t < C2; ++t)
+            if (first + t < last) red[wave][first + t] = r2[t];
     }
     __syncthreads();
     if (wave == 0 && lane < C) out[lane] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
@@ -425,131 +774,140 @@ __device__ inline float vol_at(const float* __restrict__ v, const GeoScalars& s,
 }
 
 template <int KIND>
-__global__ __launch_bounds__(kSfBx * kSfBy, KIND == kFpDD ? 4 : 1) void sf_fwd_grad_kernel(GeoScalars s, int V,
+__global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_fwd_grad_kernel(GeoScalars s, int V,
                                                                     const ViewGeo* __restrict__ views,
                                                                     const float* __restrict__ vol,
                                                                     const float* __restrict__ grad_proj,
                                                                     float* __restrict__ partials)
 {
     __shared__ float red[kSfBy][kRdChannels];
+    __shared__ float G[kSfCol][3][kSfBx * kSfBy];
     const int i = blockIdx.x * kSfBx + threadIdx.x;
     const int j = blockIdx.y * kSfBy + threadIdx.y;
-    const int kb = blockIdx.z * kSfCol;
+    const int kb = blockIdx.z * kSfCol, nk = min(kSfCol, s.nz - kb);
     const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int nblk = gridDim.x * gridDim.y * gridDim.z;
-    const bool active = i < s.nx && j < s.ny;
+    const int tid = threadIdx.y * kSfBx + threadIdx.x;
     // central-difference gradient (index units: half the neighbour difference)
-    float G[kSfCol][3];
-#pragma unroll
-    for (int kk = 0; kk < kSfCol; ++kk) {
-        const int k = kb + kk;
-        const bool in = active && k < s.nz;
-        G[kk][0] = in ? 0.5f * (vol_at(vol, s, i + 1, j, k) - vol_at(vol, s, i - 1, j, k)) : 0.0f;
-        G[kk][1] = in ? 0.5f * (vol_at(vol, s, i, j + 1, k) - vol_at(vol, s, i, j - 1, k)) : 0.0f;
-        G[kk][2] = in ? 0.5f * (vol_at(vol, s, i, j, k + 1) - vol_at(vol, s, i, j, k - 1)) : 0.0f;
-    }
+    bool any = false;
+    if (i < s.nx && j < s.ny)
+        for (int kk = 0; kk < nk; ++kk) {
+            const int k = kb + kk;
+            const float gx = 0.5f * (vol_at(vol, s, i + 1, j, k) - vol_at(vol, s, i - 1, j, k));
+            const float gy = 0.5f * (vol_at(vol, s, i, j + 1, k) - vol_at(vol, s, i, j - 1, k));
+            const float gz = 0.5f * (vol_at(vol, s, i, j, k + 1) - vol_at(vol, s, i, j, k - 1));
+            G[kk][0][tid] = gx;
+            G[kk][1][tid] = gy;
+            G[kk][2][tid] = gz;
+            any = any || !(gx == 0.0f && gy == 0.0f && gz == 0.0f);
+        }
     const float pi = (float)i - 0.5f * (s.nx - 1), pj = (float)j - 0.5f * (s.ny - 1);
     for (int v = 0; v < V; ++v) {
         const ViewGeo& g = views[v];
-        double src[3];
-        const int dom = sf_source(g, s, src);
-        const float* w = grad_proj + (size_t)v * s.nu * s.nv;
         float r[kRdChannels];
 #pragma unroll
         for (int ch = 0; ch < kRdChannels; ++ch) r[ch] = 0.0f;
-        if (active) {
+        if (any) {  // columns of a uniform region need no projection
+            double src[3];
+            const int dom = sf_source(g, s, src);
+            const SfImage w{grad_proj + (size_t)v * s.nu * s.nv, s.nu};
             const SfColumn col = sf_column<KIND>(g, s, src, dom, i, j, kb + kSfCol / 2);
-#pragma unroll
-            for (int kk = 0; kk < kSfCol; ++kk) {
-                const int k = kb + kk;
-                if (k >= s.nz) break;
-                if (G[kk][0] == 0.0f && G[kk][1] == 0.0f && G[kk][2] == 0.0f) continue;
-                SfFootprint f;
-                if (!sf_voxel<KIND>(col, g, s, src, dom, i, j, k, f)) continue;
-                const float sj = sf_gather(f, w, s.nu);
-                const float pk = (float)k - 0.5f * (s.nz - 1);
-                const float gx = sj * G[kk][0], gy = sj * G[kk][1], gz = sj * G[kk][2];
-                // B_c, then T_xy, T_xz, T_yx, T_yz, T_zx, T_zy (T_ac = sum s P_a G_c)
-                r[0] += gx; r[1] += gy; r[2] += gz;
-                r[3] = fmaf(pi, gy, r[3]); r[4] = fmaf(pi, gz, r[4]);
-                r[5] = fmaf(pj, gx, r[5]); r[6] = fmaf(pj, gz, r[6]);
-                r[7] = fmaf(pk, gx, r[7]); r[8] = fmaf(pk, gy, r[8]);
-            }
+            sf_walk<KIND>(
+                col, g, s, src, dom, i, j, kb, nk, w,
+                [&](int kk) {
+                    return !(G[kk][0][tid] == 0.0f && G[kk][1][tid] == 0.0f && G[kk][2][tid] == 0.0f);
+                },
+                [&](int kk, int k, const float (&sj)[1]) {
+                    const float pk = (float)k - 0.5f * (s.nz - 1);
+                    const float gx = sj[0] * G[kk][0][tid], gy = sj[0] * G[kk][1][tid],
+                                gz = sj[0] * G[kk][2][tid];
+                    // B_c, then T_xy, T_xz, T_yx, T_yz, T_zx, T_zy (T_ac = sum s P_a G_c)
+                    r[0] += gx; r[1] += gy; r[2] += gz;
+                    r[3] = fmaf(pi, gy, r[3]); r[4] = fmaf(pi, gz, r[4]);
+                    r[5] = fmaf(pj, gx, r[5]); r[6] = fmaf(pj, gz, r[6]);
+                    r[7] = fmaf(pk, gx, r[7]); r[8] = fmaf(pk, gy, r[8]);
+                });
         }
-        sf_reduce_store<kRdChannels>(r, red, partials + ((size_t)v * nblk + blk) * kRdChannels);
+        float r1[(kRdChannels + 1) / 2];
+        sf_halve(r, r1, (threadIdx.x & 32) != 0, 32);
+        sf_reduce_half<kRdChannels>(r1, red, partials + ((size_t)v * nblk + blk) * kRdChannels);
     }
 }
 
-// Views [v0, v0 + Vc); proj4 holds this chunk's detector gradient images.
+// Views [v0, v0 + Vc); grad_img holds this chunk's detector gradient images.
 template <int KIND>
-__global__ __launch_bounds__(kSfBx * kSfBy, KIND == kFpDD ? 4 : 1) void sf_bp_grad_kernel(GeoScalars s, int v0, int Vc,
+__global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_bp_grad_kernel(GeoScalars s, int v0, int Vc,
                                                                    const ViewGeo* __restrict__ views,
-                                                                   const float4* __restrict__ proj4,
+                                                                   const float2* __restrict__ grad_img,
                                                                    const float* __restrict__ grad_vol,
                                                                    float* __restrict__ partials)
 {
     __shared__ float red[kSfBy][kVdChannels];
+    __shared__ float E[kSfCol][kSfBx * kSfBy];
     const int i = blockIdx.x * kSfBx + threadIdx.x;
     const int j = blockIdx.y * kSfBy + threadIdx.y;
-    const int kb = blockIdx.z * kSfCol;
+    const int kb = blockIdx.z * kSfCol, nk = min(kSfCol, s.nz - kb);
     const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int nblk = gridDim.x * gridDim.y * gridDim.z;
-    const bool active = i < s.nx && j < s.ny;
-    const int NU = s.nu + 2 * kPadD, NV = s.nv + 2 * kPadD;
-    float e[kSfCol];
-#pragma unroll
-    for (int kk = 0; kk < kSfCol; ++kk)
-        e[kk] = (active && kb + kk < s.nz) ? grad_vol[((size_t)(kb + kk) * s.ny + j) * s.nx + i] : 0.0f;
+    const int tid = threadIdx.y * kSfBx + threadIdx.x;
+    bool any = false;
+    if (i < s.nx && j < s.ny)
+        for (int kk = 0; kk < nk; ++kk) {
+            const float e = grad_vol[((size_t)(kb + kk) * s.ny + j) * s.nx + i];
+            E[kk][tid] = e;
+            any = any || e != 0.0f;
+        }
     const float pi = (float)i - 0.5f * (s.nx - 1), pj = (float)j - 0.5f * (s.ny - 1);
     for (int vv = 0; vv < Vc; ++vv) {
         const int v = v0 + vv;
         const ViewGeo& g = views[v];
-        double src[3];
-        const int dom = sf_source(g, s, src);
-        const float4* img = proj4 + (size_t)vv * NU * NV;
         float A1 = 0.f, A2 = 0.f, A3 = 0.f, Z1 = 0.f, Z2 = 0.f, Z3 = 0.f;
-        const SfColumn col = sf_column<KIND>(g, s, src, dom, i, j, kb + kSfCol / 2);
-#pragma unroll
-        for (int kk = 0; kk < kSfCol; ++kk) {
-            const int k = kb + kk;
-            if (k >= s.nz || e[kk] == 0.0f) continue;
-            SfFootprint f;
-            if (!sf_voxel<KIND>(col, g, s, src, dom, i, j, k, f)) continue;
-            float da = 0.0f, db = 0.0f;
-            sf_for_each(f, [&](int a, int b, float w) {
-                const float4 p = img[(size_t)(b + kPadD) * NU + (a + kPadD)];
-                da = fmaf(w, p.y, da);
-                db = fmaf(w, p.z, db);
-            });
-            da *= f.L;
-            db *= f.L;
-            // projection of the voxel centre: offsets from the detector centre (pixels), depth
-            float ap, bp, Wc;
-            if (col.fast) {
-                const float dk = (float)k - col.ka;
-                Wc = fmaf(dk, col.pwz, col.bw);
-                const float iw = __builtin_amdgcn_rcpf(Wc);
-                ap = col.uco + fmaf(dk * col.ucn, iw, col.ucfr);
-                bp = col.bco + fmaf(dk * col.bn, iw, col.bfr);
-            } else {
-                const double fi = i, fj = j, fk = k;
-                const double U = fma(g.PUd[0], fi, fma(g.PUd[1], fj, fma(g.PUd[2], fk, g.PUd[3])));
-                const double Vv = fma(g.PVd[0], fi, fma(g.PVd[1], fj, fma(g.PVd[2], fk, g.PVd[3])));
-                const double W = fma(g.PWd[0], fi, fma(g.PWd[1], fj, fma(g.PWd[2], fk, g.PWd[3])));
-                Wc = (float)W;
-                ap = (float)(U / W);
-                bp = (float)(Vv / W);
-            }
-            const float ec = e[kk] * __builtin_amdgcn_rcpf(Wc);
-            const float c1 = ec * da, c2 = ec * db;
-            const float c3 = -ec * fmaf(da, ap, db * bp);
-            const float pk = (float)k - 0.5f * (s.nz - 1);
-            A1 += c1; A2 += c2; A3 += c3;
-            Z1 = fmaf(c1, pk, Z1); Z2 = fmaf(c2, pk, Z2); Z3 = fmaf(c3, pk, Z3);
+        if (any) {
+            double src[3];
+            const int dom = sf_source(g, s, src);
+            const SfGradImage img{grad_img + (size_t)vv * s.nu * s.nv, s.nu};
+            const SfColumn col = sf_column<KIND>(g, s, src, dom, i, j, kb + kSfCol / 2);
+            sf_walk<KIND>(
+                col, g, s, src, dom, i, j, kb, nk, img, [&](int kk) { return E[kk][tid] != 0.0f; },
+                [&](int kk, int k, const float (&d)[2]) {
+                    const float da = d[0], db = d[1];
+                    // projection of the voxel centre: offsets from the detector centre (pixels), depth
+                    float ap, bp, Wc;
+                    if (col.fast) {
+                        const float dk = (float)k - col.ka;
+                        Wc = fmaf(dk, col.pwz, col.bw);
+                        const float iw = __builtin_amdgcn_rcpf(Wc);
+                        ap = col.uco + fmaf(dk * col.ucn, iw, col.ucfr);
+                        bp = col.bco + fmaf(dk * col.bn, iw, col.bfr);
+                    } else {
+                        const double fi = i, fj = j, fk = k;
+                        const double U = fma(g.PUd[0], fi, fma(g.PUd[1], fj, fma(g.PUd[2], fk, g.PUd[3])));
+                        const double Vv = fma(g.PVd[0], fi, fma(g.PVd[1], fj, fma(g.PVd[2], fk, g.PVd[3])));
+                        const double W = fma(g.PWd[0], fi, fma(g.PWd[1], fj, fma(g.PWd[2], fk, g.PWd[3])));
+                        Wc = (float)W;
+                        ap = (float)(U / W);
+                        bp = (float)(Vv / W);
+                    }
+                    const float ec = E[kk][tid] * __builtin_amdgcn_rcpf(Wc);
+                    const float c1 = ec * da, c2 = ec * db;
+                    const float c3 = -ec * fmaf(da, ap, db * bp);
+                    const float pk = (float)k - 0.5f * (s.nz - 1);
+                    A1 += c1; A2 += c2; A3 += c3;
+                    Z1 = fmaf(c1, pk, Z1); Z2 = fmaf(c2, pk, Z2); Z3 = fmaf(c3, pk, Z3);
+                });
         }
-        float r[kVdChannels] = {A1, A2, A3, pi * A1, pi * A2, pi * A3,
-                                pj * A1, pj * A2, pj * A3, Z1, Z2, Z3};
-        sf_reduce_store<kVdChannels>(r, red, partials + ((size_t)v * nblk + blk) * kVdChannels);
+        // channels A, pi A, pj A, Z: lanes 0 .. 31 keep the first six.  A
+        // lower lane's product with its (pi, pj) is added unrounded.
+        const bool high = (threadIdx.x & 32) != 0;
+        const float A[3] = {A1, A2, A3}, Z[3] = {Z1, Z2, Z3};
+        float r1[kVdChannels / 2];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const float ra = __shfl_xor(A[t], 32), rb = __shfl_xor(high ? pi * A[t] : Z[t], 32);
+            r1[t] = high ? fmaf(pj, ra, pj * A[t]) : A[t] + ra;
+            r1[3 + t] = high ? Z[t] + rb : fmaf(pi, A[t], rb);
+        }
+        sf_reduce_half<kVdChannels>(r1, red, partials + ((size_t)v * nblk + blk) * kVdChannels);
     }
 }
 
@@ -613,11 +971,11 @@ void launch_sf_fwd_grad(const GeoScalars& s, int V, const ViewGeo* views, const 
 }
 
 void launch_sf_bp_grad(const GeoScalars& s, int v0, int Vc, const ViewGeo* views,
-                       const float4* proj4, const float* grad_vol, float* partials, int kind,
+                       const float2* grad_img, const float* grad_vol, float* partials, int kind,
                        hipStream_t st)
 {
     prof_begin(DP_K_SF, st);
-    DP_FP_LAUNCH(sf_bp_grad_kernel, s, v0, Vc, views, proj4, grad_vol, partials);
+    DP_FP_LAUNCH(sf_bp_grad_kernel, s, v0, Vc, views, grad_img, grad_vol, partials);
     prof_end(DP_K_SF, st);
 }
 #undef DP_FP_LAUNCH

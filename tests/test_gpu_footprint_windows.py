@@ -1,0 +1,71 @@
+"""Footprint gathers and scatter at the edges of their pixel windows: windows
+of one quad, of several quads, taller than five rows, detectors narrower than a
+quad, and pixels of weight zero that hold no number.  Same bars as
+test_gpu_footprint.py."""
+import math
+
+import numpy as np
+import pytest
+
+import synth
+from synth import Geom
+from test_gpu_parity import check_grads, check_values, f32, f64
+
+pytestmark = pytest.mark.gpu
+
+# voxel widths on the detector: 1.5 px (one quad), 5.5 px (several quads, row
+# counts around five), 9 px (pixel by pixel); detectors of 3, 4 and 5 columns;
+# columns and rows past the detector's edges in all of them
+CASES = {
+    "one-quad": Geom(21, 18, 19, 1.0, 1.0, 1.0, 23, 21, 1.0, 1.0, off_u=2.5, off_v=-1.25),
+    "quads": Geom(11, 10, 9, 2.0, 2.0, 2.0, 52, 47, 0.55, 0.55, off_u=-3.5),
+    "pixels": Geom(9, 8, 7, 2.0, 2.0, 2.0, 70, 61, 0.33, 0.33, off_v=4.0),
+    "tall": Geom(10, 9, 8, 1.0, 1.0, 3.0, 16, 60, 1.0, 0.6),
+    "nu3": Geom(12, 11, 10, 1.0, 1.0, 1.0, 3, 14, 2.0, 1.0),
+    "nu4": Geom(12, 11, 10, 1.0, 1.0, 1.0, 4, 1, 2.0, 9.0),
+    "nu5": Geom(70, 5, 17, 0.5, 1.0, 1.0, 5, 2, 4.0, 5.0),
+}
+
+
+@pytest.mark.parametrize("kind", ["sf", "dd"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_windows_match_oracle(dp, oracle, name, kind):
+    g, V = CASES[name], 3
+    rng = synth.rng_for(760 + list(CASES).index(name))
+    vol = rng.uniform(0.0, 0.05, g.vol_shape).astype(np.float32)
+    vol[:, : g.ny // 2, : g.nx // 3] = 0.0  # voxels without a footprint to scatter
+    angles, poses = rng.uniform(0, 2 * math.pi, V), synth.random_poses(V, 2.0, 9.0, rng)
+    a, p = f64(angles), f64(poses)
+    img = rng.standard_normal((V, g.nv, g.nu)).astype(np.float32)
+    e = rng.standard_normal(g.vol_shape).astype(np.float32)
+    check_values(f"{name} {kind} project", dp.fp_project(g, a, p, f32(vol), kind).cpu().numpy(),
+                 oracle.fp_project(g, angles, poses, vol, kind))
+    check_values(f"{name} {kind} backproject", dp.fp_backproject(g, a, p, f32(img), kind).cpu().numpy(),
+                 oracle.fp_backproject(g, angles, poses, img, kind))
+    check_grads(f"{name} {kind} project_grad_pose",
+                dp.fp_project_grad_pose(g, a, p, f32(vol), f32(img), kind).cpu().numpy(),
+                oracle.fp_project_grad_pose(g, angles, poses, vol, img, kind))
+    check_grads(f"{name} {kind} backproject_grad_pose",
+                dp.fp_backproject_grad_pose(g, a, p, f32(img), f32(e), kind).cpu().numpy(),
+                oracle.fp_backproject_grad_pose(g, angles, poses, img, e, kind))
+
+
+@pytest.mark.parametrize("value", [math.inf, math.nan])
+@pytest.mark.parametrize("kind", ["sf", "dd"])
+def test_pixel_without_a_number_reaches_its_voxels_only(dp, oracle, kind, value):
+    g = CASES["one-quad"]
+    rng = synth.rng_for(780)
+    angles, poses = np.array([0.4]), synth.random_poses(1, 1.0, 4.0, rng)
+    img = rng.standard_normal((1, g.nv, g.nu)).astype(np.float32)
+    img[0, 9, 11] = 0.0
+    clean = dp.fp_backproject(g, f64(angles), f64(poses), f32(img), kind).cpu().numpy()
+    img[0, 9, 11] = value
+    got = dp.fp_backproject(g, f64(angles), f64(poses), f32(img), kind).cpu().numpy()
+    ind = np.zeros_like(img)
+    ind[0, 9, 11] = 1.0
+    w = oracle.fp_backproject(g, angles, poses, ind, kind)
+    away, hit = w == 0.0, w > 1e-4 * w.max()
+    # a voxel whose footprint ends within rounding of the pixel's edge may touch it
+    assert np.mean(np.isfinite(got[away])) > 0.999 and not np.isfinite(got[hit]).any()
+    ok = away & np.isfinite(got)
+    np.testing.assert_array_equal(got[ok], clean[ok])
