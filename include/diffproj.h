@@ -336,6 +336,18 @@ size_t dp_conv3x3_wgrad_ws_bytes(int32_t N, int32_t H, int32_t W, int32_t Ci, in
 int dp_conv3x3_wgrad_bf16(int32_t N, int32_t H, int32_t W, int32_t Ci, int32_t Co,
                           int32_t stride, const void* x, const void* dz, int32_t ldw,
                           int32_t ones, float* dw, void* ws, size_t ws_bytes, void* stream);
+/* The first layer: the same convolution and weight gradient for a two-channel
+ * input x [N][H][W][2] BF16 (4-byte aligned), Co a multiple of 32, weight rows
+ * w [Co][ldw], ldw a multiple of 8 and at least 24; w, dz and y 16-byte aligned.
+ * dw [Co][ldw] FP32: the 18 weights' gradients, the bias gradient in column 18,
+ * zeros; ws: dp_gemm_bf16_ws_bytes(Co, ldw, N Ho Wo) bytes.  The same values
+ * as dp_im2col3x3_ld_bf16 with the ones column and the products above it. */
+int dp_conv3x3_c2_fwd_bf16(int32_t N, int32_t H, int32_t W, int32_t Co, int32_t stride, const void* x,
+                           const void* w, int32_t ldw, const float* bias, int32_t bias_stride,
+                           int32_t relu, void* y, void* stream);
+int dp_conv3x3_c2_wgrad_bf16(int32_t N, int32_t H, int32_t W, int32_t Co, int32_t stride, const void* x,
+                             const void* dz, int32_t ldw, float* dw, void* ws, size_t ws_bytes,
+                             void* stream);
 /* dp_conv3x3_dgrad_act_bf16: the input gradient dx [N][H][W][Ci] of
  *   sum(dz . conv(x)), followed by the activation backward of the layer
  *   below: out BF16 = dx * (y > 0) if relu (y [N][H][W][Ci] BF16, that

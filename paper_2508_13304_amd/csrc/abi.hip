@@ -1043,6 +1043,51 @@ int dp_conv3x3_wgrad_bf16(int32_t N, int32_t H, int32_t W, int32_t Ci, int32_t C
     return check_launch("dp_conv3x3_wgrad_bf16");
 }
 
+// Shared checks of the two-channel convolutions.
+static int conv_c2_args(int32_t N, int32_t H, int32_t W, int32_t Co, int32_t stride, int32_t ldw, const char* what)
+{
+    int rc = conv_dims(N, H, W, 2, stride);
+    if (rc) return rc;
+    if (Co <= 0 || Co % 32) return fail(DP_ERR_ARG, "%s: Co must be a multiple of 32", what);
+    if (ldw % 8 || ldw < 24) return fail(DP_ERR_ARG, "%s: ldw %d must be a multiple of 8, at least 24", what, ldw);
+    const int64_t Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
+    if ((int64_t)N * Ho * Wo * Co >= ((int64_t)1 << 31) || (int64_t)Co * ldw >= ((int64_t)1 << 31) || Co / 32 > 65535)
+        return fail(DP_ERR_UNSUPPORTED, "%s: tensor above 2^31 elements; split the batch", what);
+    return DP_OK;
+}
+
+int dp_conv3x3_c2_fwd_bf16(int32_t N, int32_t H, int32_t W, int32_t Co, int32_t stride, const void* x,
+                           const void* w, int32_t ldw, const float* bias, int32_t bias_stride,
+                           int32_t relu, void* y, void* stream)
+{
+    int rc = conv_c2_args(N, H, W, Co, stride, ldw, "conv3x3_c2_fwd");
+    if (rc) return rc;
+    if (!x || !w || !bias || !y) return fail(DP_ERR_ARG, "conv3x3_c2_fwd: NULL pointer");
+    if (bias_stride < 1) return fail(DP_ERR_ARG, "conv3x3_c2_fwd: bias_stride must be positive");
+    if (((uintptr_t)x & 3) || !aligned16(w) || !aligned16(y))
+        return fail(DP_ERR_ARG, "conv3x3_c2_fwd: misaligned pointer");
+    (void)hipGetLastError();
+    launch_conv2_fwd(N, H, W, Co, stride, x, w, ldw, bias, bias_stride, relu != 0, y, (hipStream_t)stream);
+    return check_launch("dp_conv3x3_c2_fwd_bf16");
+}
+
+int dp_conv3x3_c2_wgrad_bf16(int32_t N, int32_t H, int32_t W, int32_t Co, int32_t stride, const void* x,
+                             const void* dz, int32_t ldw, float* dw, void* ws, size_t ws_bytes,
+                             void* stream)
+{
+    int rc = conv_c2_args(N, H, W, Co, stride, ldw, "conv3x3_c2_wgrad");
+    if (rc) return rc;
+    if (!x || !dz || !dw) return fail(DP_ERR_ARG, "conv3x3_c2_wgrad: NULL pointer");
+    if (((uintptr_t)x & 3) || !aligned16(dz)) return fail(DP_ERR_ARG, "conv3x3_c2_wgrad: misaligned pointer");
+    const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
+    const size_t need = gemm_ws_bytes(Co, ldw, N * Ho * Wo);
+    if (need && (!ws || ws_bytes < need))
+        return fail(DP_ERR_ARG, "conv3x3_c2_wgrad: workspace of %zu bytes needed, %zu given", need, ws_bytes);
+    (void)hipGetLastError();
+    launch_conv2_wgrad(N, H, W, Co, stride, x, dz, ldw, dw, (float*)ws, ws_bytes, (hipStream_t)stream);
+    return check_launch("dp_conv3x3_c2_wgrad_bf16");
+}
+
 int dp_conv3x3_dgrad_act_bf16(int32_t N, int32_t H, int32_t W, int32_t Ci, int32_t Co,
                               int32_t stride, const void* dz, const void* w, int32_t ldw,
                               const void* y, int32_t relu, void* out, void* stream)

@@ -63,10 +63,13 @@ def _lib():
         lib.dp_conv3x3_wgrad_ws_bytes.restype = sz
         lib.dp_conv3x3_wgrad_bf16.argtypes = [i32] * 6 + [vp, vp, i32, i32, vp, vp, sz, vp]
         lib.dp_conv3x3_dgrad_act_bf16.argtypes = [i32] * 6 + [vp, vp, i32, vp, i32, vp, vp]
+        lib.dp_conv3x3_c2_fwd_bf16.argtypes = [i32] * 5 + [vp, vp, i32, vp, i32, i32, vp, vp]
+        lib.dp_conv3x3_c2_wgrad_bf16.argtypes = [i32] * 5 + [vp, vp, i32, vp, vp, sz, vp]
         for f in ("dp_gemm_bf16", "dp_gemm_bf16_ws", "dp_gemm_bias_act_bf16", "dp_im2col3x3_bf16",
                   "dp_im2col3x3_ld_bf16", "dp_col2im3x3", "dp_col2im3x3_act_bf16",
                   "dp_bias_act_bf16", "dp_act_bwd_bf16", "dp_colsum_bf16", "dp_adam_f32",
-                  "dp_conv3x3_fwd_bf16", "dp_conv3x3_wgrad_bf16", "dp_conv3x3_dgrad_act_bf16"):
+                  "dp_conv3x3_fwd_bf16", "dp_conv3x3_wgrad_bf16", "dp_conv3x3_dgrad_act_bf16",
+                  "dp_conv3x3_c2_fwd_bf16", "dp_conv3x3_c2_wgrad_bf16"):
             getattr(lib, f).restype = C.c_int
         lib._cnn_ready = True
     return lib
@@ -192,6 +195,36 @@ def conv_wgrad(x, dz, stride, out, ones=True):
     return out
 
 
+def conv_c2_fwd(x, w, stride, bias, relu=True):
+    """conv_fwd for a two-channel x [N][H][W][2] and weight rows w [Co][>= 24],
+    Co a multiple of 32."""
+    x = x.contiguous()
+    N, H, W, _ = x.shape
+    Co = w.shape[0]
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    y = torch.empty((N, Ho, Wo, Co), dtype=torch.bfloat16, device=x.device)
+    _check(_lib().dp_conv3x3_c2_fwd_bf16(N, H, W, Co, stride, _p(x), _p(w), _ld(w), _p(bias),
+                                         bias.stride(0), int(relu), _p(y), _stream(None)),
+           "dp_conv3x3_c2_fwd_bf16")
+    return y
+
+
+def conv_c2_wgrad(x, dz, stride, out):
+    """conv_wgrad (with the bias gradient in column 18) for a two-channel x."""
+    x, dz = x.contiguous(), dz.contiguous()
+    N, H, W, _ = x.shape
+    Co, ld = out.shape
+    assert out.stride(1) == 1 and out.stride(0) == ld
+    lib = _lib()
+    need = lib.dp_gemm_bf16_ws_bytes(Co, ld, dz.numel() // Co)
+    ws = _workspace(x.device, need) if need else None
+    _check(lib.dp_conv3x3_c2_wgrad_bf16(N, H, W, Co, stride, _p(x), _p(dz), ld, _p(out),
+                                        _p(ws) if ws is not None else None,
+                                        ws.numel() if ws is not None else 0, _stream(None)),
+           "dp_conv3x3_c2_wgrad_bf16")
+    return out
+
+
 def conv_dgrad_act(dz, w, shape, stride, y=None, relu=True):
     """BF16 input gradient of a 3x3 convolution for dz [N][Ho][Wo][Co], weight
     rows w [Co][>= 9 Ci], times (y > 0) for the layer below's output y if
@@ -303,6 +336,14 @@ class ProposalNet:
             ps += [W, b]
         return ps + [self.Wfc, self.bfc]
 
+    @staticmethod
+    def _gathers(x, co):
+        """Whether a 2-channel input can take the gathering kernels (whole pixels of
+        4 aligned bytes, 32 channels at a time, 32-bit indices)."""
+        n, h, w, _ = x.shape
+        out = n * ((h - 1) // 2 + 1) * ((w - 1) // 2 + 1) * co
+        return co % 32 == 0 and x.data_ptr() % 4 == 0 and out < 2 ** 31
+
     def forward(self, x, keep=False):
         """x: [N][H][W][2] BF16 (NHWC).  Returns FP32 [N][6] (and the cache)."""
         cache = []
@@ -313,10 +354,13 @@ class ProposalNet:
                 # implicit GEMM: the products gather their operand tiles from h
                 y = conv_fwd(h, self.bblocks[li], s, b, relu=True)
                 col = None
+            elif h.shape[3] == 2 and self._gathers(h, W.shape[0]):
+                # the 2-channel input layer: one product step, gathered directly
+                y = conv_c2_fwd(h, self.bblocks[li], s, b, relu=True)
+                col = None
             else:
-                # few input channels (the 2-channel input layer): im2col rows
-                # padded to the parameter row, with a ones column for the
-                # bias gradient
+                # other channel counts: im2col rows padded to the parameter row,
+                # with a ones column for the bias gradient
                 col, Ho, Wo = im2col(h, s, ld=self.blocks[li].shape[1], ones=keep)
                 y = gemm_bias_act(col, self.bblocks[li], K, b, relu=True)
                 y = y.view(h.shape[0], Ho, Wo, W.shape[0])
@@ -344,7 +388,9 @@ class ProposalNet:
             dz = dz.reshape(-1, W.shape[0])
             K = W.shape[1]
             # [Co][row]: dW | db | 0
-            if col is None:
+            if col is None and x_in.shape[3] == 2:
+                conv_c2_wgrad(x_in, dz, s, out=self.gblocks[li])
+            elif col is None:
                 conv_wgrad(x_in, dz, s, out=self.gblocks[li], ones=True)
             else:
                 gemm(dz, col, ta=True, out=self.gblocks[li])
