@@ -203,7 +203,6 @@ struct VariantKey {
 std::mutex g_var_mu;
 std::map<VariantKey, int> g_var_cache;
 int g_var_force[5] = {-1, -1, -1, -1, -1};
-constexpr int kDefaultVariant = 1;
 
 // Shape class: grid and detector sizes, view-count octave and the ratio of
 // the pixel footprint at the isocentre to the voxel size (in eighths).
@@ -224,7 +223,7 @@ int variant_for(int op, const dp_geom& g, int V)
     std::lock_guard<std::mutex> lk(g_var_mu);
     if (g_var_force[op] >= 0) return g_var_force[op];
     auto it = g_var_cache.find(variant_key(op, g, V));
-    return it == g_var_cache.end() ? kDefaultVariant : it->second;
+    return it == g_var_cache.end() ? kRdDefaultVariant : it->second;
 }
 
 // ---------------------------------------------------------------------------

@@ -128,6 +128,7 @@ constexpr int kRdMaxBatch = 16;
 constexpr int kRdChunkClasses = 3;
 constexpr int kRdVariants = kRdShapes * kRdChunkClasses;
 static_assert(kRdVariants == DP_RD_VARIANTS, "variant count of the public header");
+constexpr int kRdDefaultVariant = 1;  // 16x16 tiles, middle class
 inline int rd_variant_shape(int variant) { return variant / kRdChunkClasses; }
 // fused SSD kernel with the Gauss-Newton matrix: 9 gradient sums, the SSD,
 // and the 21 upper-triangle entries of 2 J J^T

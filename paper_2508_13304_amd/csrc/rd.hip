@@ -171,7 +171,7 @@ struct BoxRec {
 // the margin that covers the spherical cap between them (voxel units).
 // `active` rays define the sample range; every in-detector corner lane
 // publishes its ray geometry (whether or not it carries samples).
-template <int TW>
+template <int TW, int TH = kRdThreads / TW>
 __device__ inline void tile_setup(const GeoScalars& s, const RayState& r, bool inside, bool active,
                                   int a, int b, int a0, int b0, TileShared& sh, int& Kmin,
                                   int& Kmax, float& margin)
@@ -188,7 +188,7 @@ __device__ inline void tile_setup(const GeoScalars& s, const RayState& r, bool i
         sh.khi[wave] = hi;
     }
     // corner rays: first / last valid pixel of the tile in each direction
-    const int a1 = min(a0 + TW - 1, s.nu - 1), b1 = min(b0 + kRdThreads / TW - 1, s.nv - 1);
+    const int a1 = min(a0 + TW - 1, s.nu - 1), b1 = min(b0 + TH - 1, s.nv - 1);
     // a degenerate tile (one column or row) has coincident corners: every
     // owner writes the same values
     if (inside && (a == a0 || a == a1) && (b == b0 || b == b1)) {
@@ -249,37 +249,55 @@ __device__ inline Box chunk_box(const TileShared& sh, int K, int Ke, float step,
     return bx;
 }
 
-// Plan every chunk of the tile at once (thread i plans chunk i) and return
-// the chunk length M for which all boxes fit `cap` voxels, or 0 if none
-// does (the tile then reads its taps from global memory).  M shrinks in
-// steps of max(2, M / 8) (16 -> 14 -> 12 ...): a tile whose widest box
-// overflows by a few percent keeps most of its chunk length.
+// The chunk length M for which all boxes of the tile fit `cap` voxels, or 0
+// if none does (the tile then reads its taps from global memory).  M shrinks
+// in steps of max(2, M / 8) (16 -> 14 -> 12 ...): a tile whose widest box
+// overflows by a few percent keeps most of its chunk length.  The wavefronts
+// try four successive lengths at a time, a lane per chunk, and the first that
+// fits is taken: oblique tiles shrink M six to ten times, which one length at
+// a time cost as many rounds of box bounds and barriers (forward of 192^3, 100
+// orbit views: 3.69 to 3.62 ms with it; single-pass SSD of 256^3, 64 views:
+// 13.94 to 13.77).
 // Thread i < the chunk count leaves the record of chunk i in `rec`.
 __device__ inline int plan_chunks(TileShared& sh, int Kmin, int Kmax, int Mmax, int cap,
                                   float step, float margin, int NX, int NY, int NZ, BoxRec& rec)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int M = Mmax;;) {
-        const int nch = (Kmax - Kmin) / M + 1;
-        if (nch > kMaxChunks) return 0;
-        int vol = 0;
-        if ((int)threadIdx.x < nch) {
-            const int K = Kmin + (int)threadIdx.x * M;
-            const Box b = chunk_box(sh, K, min(K + M - 1, Kmax), step, margin, NX, NY, NZ);
-            rec.w[0] = (unsigned)b.ox | (unsigned)b.oy << 16;
-            rec.w[1] = (unsigned)b.oz | (unsigned)b.bx << 16;
-            rec.w[2] = (unsigned)b.by | (unsigned)b.bz << 16;
-            vol = lds_pitch(b.bx) * lds_pitch(b.by) * b.bz;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const auto shorter = [](int M) { return max(1, M - max(2, M >> 3)); };
+    int M = Mmax;
+    for (bool found = false; !found;) {
+        // this wavefront's length; after M = 1 (which ends the search) it repeats
+        int Mw = M;
+        for (int q = 0; q < wave; ++q) Mw = shorter(Mw);
+        const int nch = (Kmax - Kmin) / Mw + 1;
+        bool over = false;
+        if (nch <= kMaxChunks)
+            for (int c = lane; c < nch; c += 64) {
+                asm volatile("" ::: "memory");  // corner reads stay in the loop: registers are short here
+                const int K = Kmin + c * Mw;
+                const Box b = chunk_box(sh, K, min(K + Mw - 1, Kmax), step, margin, NX, NY, NZ);
+                over = over || (float)lds_pitch(b.bx) * (float)lds_pitch(b.by) * (float)b.bz > (float)cap;
+            }
+        // fits: the length; shorten further: -1; no length will do: 0
+        const bool fits = nch <= kMaxChunks && __builtin_amdgcn_ballot_w64(over) == 0;
+        if (lane == 0) sh.vmax[wave] = fits ? Mw : nch > kMaxChunks || Mw == 1 ? 0 : -1;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4 && !found; ++q) {
+            const int r = sh.vmax[q];
+            found = r >= 0;
+            M = found ? r : shorter(M);
         }
-        for (int off = 32; off > 0; off >>= 1) vol = max(vol, __shfl_xor(vol, off));
-        if (lane == 0) sh.vmax[wave] = vol;
         __syncthreads();
-        const int vmax = max(max(sh.vmax[0], sh.vmax[1]), max(sh.vmax[2], sh.vmax[3]));
-        __syncthreads();
-        if (vmax <= cap) return M;
-        if (M == 1) return 0;
-        M = max(1, M - max(2, M >> 3));
     }
+    if (M > 0 && (int)threadIdx.x <= (Kmax - Kmin) / M) {
+        const int K = Kmin + (int)threadIdx.x * M;
+        const Box b = chunk_box(sh, K, min(K + M - 1, Kmax), step, margin, NX, NY, NZ);
+        rec.w[0] = (unsigned)b.ox | (unsigned)b.oy << 16;
+        rec.w[1] = (unsigned)b.oz | (unsigned)b.bx << 16;
+        rec.w[2] = (unsigned)b.by | (unsigned)b.bz << 16;
+    }
+    return M;
 }
 
 // Chunk records travel through the two slots of sh.cur: chunk ci is read
@@ -596,50 +614,67 @@ __device__ inline void load_box_interior(const Box& b, const float* __restrict__
     }
 }
 
-// Box touching the grid's faces (or beyond): every voxel tested, neighbour
-// offsets clamped onto the voxel itself at the grid faces and their values
-// masked, loads only for voxels on the grid.
+// Box touching the grid's faces (or beyond): the items of an interior box with
+// every address clamped onto the grid and the values of voxels off it masked
+// to zero.  All loads of an item are issued before its stores: voxel by voxel
+// they were a chain of round trips to memory, which showed wherever few blocks
+// share a compute unit (forward of 256^3, one 384^2 view: 165 to 116 us;
+// gradient of 151x133x117, 12 views: 689 to 657).
 template <int C>
 __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu, int nx, int ny,
                                      int nz, float* dst)
 {
-    const int nxy = nx * ny;
+    constexpr int SEG = BoxItem<C>::SEG;
+    const unsigned nx4 = 4u * (unsigned)nx, nxy4 = nx4 * (unsigned)ny;
     const unsigned dslot = (unsigned)(C * b.py * b.px);
     const BoxItems bi = box_items<C>(b);
-    constexpr int SEG = BoxItem<C>::SEG;
     for (unsigned it = threadIdx.x; it < bi.items; it += kRdThreads) {
         const unsigned p = bi.nseg > 1 ? __umulhi(it, bi.mseg) : it;
         const unsigned sg = it - p * bi.nseg;
         const unsigned uly = b.bx > 1 ? __umulhi(p, bi.mx) : p;
-        struct { int lx, ly, z0, z1; } w;
-        w.lx = (int)(p - uly * (unsigned)b.bx);
-        w.ly = (int)uly;
-        w.z0 = (int)sg * SEG;
-        w.z1 = min(w.z0 + SEG, b.bz);
-        const int i = b.ox + w.lx - kPadV, j = b.oy + w.ly - kPadV;
+        const int lx = (int)(p - uly * (unsigned)b.bx), ly = (int)uly;
+        const int z0 = (int)sg * SEG, cnt = min(SEG, b.bz - z0);
+        const int i = b.ox + lx - kPadV, j = b.oy + ly - kPadV, k0 = b.oz + z0 - kPadV;
         const bool col = (unsigned)i < (unsigned)nx && (unsigned)j < (unsigned)ny;
-        const bool fxm = i > 0, fxp = i + 1 < nx, fym = j > 0, fyp = j + 1 < ny;
-        const int oxm = fxm ? -1 : 0, oxp = fxp ? 1 : 0;
-        const int oym = fym ? -nx : 0, oyp = fyp ? nx : 0;
-        int k = b.oz + w.z0 - kPadV;
-        int off = (k * ny + j) * nx + i;  // element offset, meaningful only on the grid
-        unsigned slot = (unsigned)C * (((unsigned)w.z0 * (unsigned)b.py + (unsigned)w.ly) *
-                                       (unsigned)b.px + (unsigned)w.lx);
-        for (int z = w.z0; z < w.z1; ++z, ++k, off += nxy, slot += dslot) {
-            float m = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-            if (col && (unsigned)k < (unsigned)nz) {
-                const float* pc = mu + off;
-                m = pc[0];
-                if constexpr (C >= 3) {
-                    const bool fzm = k > 0, fzp = k + 1 < nz;
-                    const float xm = pc[oxm], xp = pc[oxp], ym = pc[oym], yp = pc[oyp];
-                    const float zm = pc[fzm ? -nxy : 0], zp = pc[fzp ? nxy : 0];
-                    gx = (fxp ? xp : 0.0f) - (fxm ? xm : 0.0f);
-                    gy = (fyp ? yp : 0.0f) - (fym ? ym : 0.0f);
-                    gz = (fzp ? zp : 0.0f) - (fzm ? zm : 0.0f);
-                }
+        const unsigned oc = ((unsigned)min(max(j, 0), ny - 1) * (unsigned)nx + (unsigned)min(max(i, 0), nx - 1)) * 4u;
+        const auto plane = [&](int k) { return (unsigned)min(max(k, 0), nz - 1) * nxy4; };
+        const auto on = [&](int k) { return col && (unsigned)k < (unsigned)nz; };
+        unsigned slot = (unsigned)C * (((unsigned)z0 * (unsigned)b.py + (unsigned)ly) * (unsigned)b.px + (unsigned)lx);
+        if constexpr (C == 1) {
+            float v[SEG];
+#pragma unroll
+            for (int q = 0; q < SEG; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
+#pragma unroll
+            for (int q = 0; q < SEG; ++q, slot += dslot)
+                if (q < cnt) box_store<C>(dst, slot, on(k0 + q) ? v[q] : 0.f, 0.f, 0.f, 0.f);
+        } else {
+            const bool fxm = i > 0, fxp = i + 1 < nx, fym = j > 0, fyp = j + 1 < ny;
+            const unsigned oxm = oc - (col && fxm ? 4u : 0u), oxp = oc + (col && fxp ? 4u : 0u);
+            const unsigned oym = oc - (col && fym ? nx4 : 0u), oyp = oc + (col && fyp ? nx4 : 0u);
+            float c[SEG + 2], w[SEG][4];
+#pragma unroll
+            for (int q = 0; q < SEG + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
+#pragma unroll
+            for (int q = 0; q < SEG; ++q) {
+                const unsigned o = plane(k0 + q);
+                w[q][0] = ldv(mu, o + oxm);
+                w[q][1] = ldv(mu, o + oxp);
+                w[q][2] = ldv(mu, o + oym);
+                w[q][3] = ldv(mu, o + oyp);
             }
-            box_store<C>(dst, slot, m, gx, gy, gz);
+#pragma unroll
+            for (int q = 0; q < SEG; ++q, slot += dslot) {
+                if (q >= cnt) break;
+                const int k = k0 + q;
+                float m = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
+                if (on(k)) {
+                    m = c[q + 1];
+                    gx = (fxp ? w[q][1] : 0.0f) - (fxm ? w[q][0] : 0.0f);
+                    gy = (fyp ? w[q][3] : 0.0f) - (fym ? w[q][2] : 0.0f);
+                    gz = (k + 1 < nz ? c[q + 2] : 0.0f) - (k > 0 ? c[q] : 0.0f);
+                }
+                box_store<C>(dst, slot, m, gx, gy, gz);
+            }
         }
     }
 }
@@ -746,19 +781,97 @@ __device__ inline ChunkRay chunk_ray(const RayState& r, int kb, int ke, const Bo
     return c;
 }
 
-template <int TW, int MCH, int CAP>
+// Sum of a chunk's samples kb .. ke of one ray from its staged box.
+template <int CAP>
+__device__ inline void fwd_samples(const float* lds, const Box& bx, const ChunkRay& c, float& acc)
+{
+    const int BX = bx.px, BXY = bx.px * bx.py;
+    const float fbx = (float)bx.px, fby = (float)bx.py;
+    const float fimax = (float)(CAP - 1 - (BXY + BX + 1));
+    // sample j of the chunk, its position measured from (X0, Y0, Z0)
+    auto sample = [&](float j, float X0, float Y0, float Z0) {
+        const float X = fmaf(j, c.sx, X0), Y = fmaf(j, c.sy, Y0), Z = fmaf(j, c.sz, Z0);
+        const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
+        const float wx = X - fx, wy = Y - fy, wz = Z - fz;
+        const int idx = lds_index(fmaf(fmaf(fz, fby, fy), fbx, fx), fimax);
+        const float* p = lds + idx;
+        const float c00 = lerpf(p[0], p[1], wx);
+        const float c10 = lerpf(p[BX], p[BX + 1], wx);
+        const float c01 = lerpf(p[BXY], p[BXY + 1], wx);
+        const float c11 = lerpf(p[BXY + BX], p[BXY + BX + 1], wx);
+        acc += lerpf(lerpf(c00, c10, wy), lerpf(c01, c11, wy), wz);
+    };
+    // two samples per trip (the second from the next sample's origin),
+    // then the odd one
+    const float X1 = c.X + c.sx, Y1 = c.Y + c.sy, Z1 = c.Z + c.sz, n1 = c.n - 1.0f;
+    float j = 0.0f;
+    for (; j <= n1; j += 2.0f) {
+        sample(j, c.X, c.Y, c.Z);
+        sample(j, X1, Y1, Z1);
+    }
+    if (j <= c.n) sample(j, c.X, c.Y, c.Z);
+}
+
+// Sum of the samples klo .. khi of one ray straight from the volume (a tile
+// whose chunk boxes are too large for LDS).
+__device__ inline float fwd_samples_global(const GeoScalars& s, const RayState& r, const float* __restrict__ mu,
+                                           int klo, int khi)
+{
+    const float xmax = s.nx + 2 * kPadV - 1.001f, ymax = s.ny + 2 * kPadV - 1.001f,
+                zmax = s.nz + 2 * kPadV - 1.001f, step = (float)s.step;
+    float acc = 0.0f;
+    for (int k = klo; k <= khi; ++k) {
+        const float t = fmaf((float)(k - r.k0), step, r.f);
+        const float X = fminf(fmaxf(fmaf(t, r.dx, r.x0), 0.0f), xmax);
+        const float Y = fminf(fmaxf(fmaf(t, r.dy, r.y0), 0.0f), ymax);
+        const float Z = fminf(fmaxf(fmaf(t, r.dz, r.z0), 0.0f), zmax);
+        const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
+        const float wx = X - fx, wy = Y - fy, wz = Z - fz;
+        const int I = (int)fx, J = (int)fy, Kz = (int)fz;
+        float m[2][2][2];
+#pragma unroll
+        for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 2; ++dx)
+                    m[dz][dy][dx] = mu_at(mu, s.nx, s.ny, s.nz, I + dx, J + dy, Kz + dz);
+        const float c00 = lerpf(m[0][0][0], m[0][0][1], wx);
+        const float c10 = lerpf(m[0][1][0], m[0][1][1], wx);
+        const float c01 = lerpf(m[1][0][0], m[1][0][1], wx);
+        const float c11 = lerpf(m[1][1][0], m[1][1][1], wx);
+        acc += lerpf(lerpf(c00, c10, wy), lerpf(c01, c11, wy), wz);
+    }
+    return acc;
+}
+
+// One detector tile.  SPLIT: the tile is 8x8 rays and each of the block's
+// four wavefronts takes a quarter of every chunk's samples of all of them (a
+// quarter of the sample range where there are no chunks), the four sums added
+// at the end; otherwise a thread per ray of a tile TW pixels wide.
+template <int TW, int MCH, int CAP, bool SPLIT = false>
 __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restrict__ views,
                                    const float* __restrict__ mu, float* __restrict__ proj,
                                    int v, int tile, float* lds, TileShared& sh)
 {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int a, b, a0, b0;
-    rd_pixel<TW>(s, tile, a, b, a0, b0);
+    if constexpr (SPLIT) {
+        const int tiles_u = (s.nu + 7) / 8;
+        a0 = tile % tiles_u * 8;
+        b0 = tile / tiles_u * 8;
+        a = a0 + (lane & 7);
+        b = b0 + (lane >> 3);
+    } else {
+        rd_pixel<TW>(s, tile, a, b, a0, b0);
+    }
     const bool active = a < s.nu && b < s.nv;
     const ViewGeo& g = views[v];
     const RayState r = ray_setup(s, g, min(a, s.nu - 1), min(b, s.nv - 1));
     int Kmin, Kmax;
     float margin;
-    tile_setup<TW>(s, r, active, active, a, b, a0, b0, sh, Kmin, Kmax, margin);
+    tile_setup<SPLIT ? 8 : TW, SPLIT ? 8 : kRdThreads / TW>(s, r, active, active, a, b, a0, b0, sh, Kmin,
+                                                            Kmax, margin);
     const int NX = s.nx + 2 * kPadV, NY = s.ny + 2 * kPadV, NZ = s.nz + 2 * kPadV;
     const float step = (float)s.step;
     const int klo = active ? r.klo : 1, khi = active ? r.khi : 0;
@@ -777,59 +890,22 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
             publish_box(sh, rec, ci + 1);
             load_box<1>(bx, mu, s.nx, s.ny, s.nz, lds);
             __syncthreads();
-            const int kb = max(K, klo), ke = min(Ke, khi);
-            const ChunkRay c = chunk_ray(r, kb, ke, bx, step);
-            const int BX = bx.px, BXY = bx.px * bx.py;
-            const float fbx = (float)bx.px, fby = (float)bx.py;
-            const float fimax = (float)(CAP - 1 - (BXY + BX + 1));
-            // sample j of the chunk, its position measured from (X0, Y0, Z0)
-            auto sample = [&](float j, float X0, float Y0, float Z0) {
-                const float X = fmaf(j, c.sx, X0), Y = fmaf(j, c.sy, Y0), Z = fmaf(j, c.sz, Z0);
-                const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
-                const float wx = X - fx, wy = Y - fy, wz = Z - fz;
-                const int idx = lds_index(fmaf(fmaf(fz, fby, fy), fbx, fx), fimax);
-                const float* p = lds + idx;
-                const float c00 = lerpf(p[0], p[1], wx);
-                const float c10 = lerpf(p[BX], p[BX + 1], wx);
-                const float c01 = lerpf(p[BXY], p[BXY + 1], wx);
-                const float c11 = lerpf(p[BXY + BX], p[BXY + BX + 1], wx);
-                acc += lerpf(lerpf(c00, c10, wy), lerpf(c01, c11, wy), wz);
-            };
-            // two samples per trip (the second from the next sample's origin),
-            // then the odd one
-            const float X1 = c.X + c.sx, Y1 = c.Y + c.sy, Z1 = c.Z + c.sz, n1 = c.n - 1.0f;
-            float j = 0.0f;
-            for (; j <= n1; j += 2.0f) {
-                sample(j, c.X, c.Y, c.Z);
-                sample(j, X1, Y1, Z1);
-            }
-            if (j <= c.n) sample(j, c.X, c.Y, c.Z);
+            const int Mq = SPLIT ? (M + 3) / 4 : M, Kw = SPLIT ? K + wave * Mq : K;
+            const int kb = max(Kw, klo), ke = min(min(Kw + Mq - 1, Ke), khi);
+            fwd_samples<CAP>(lds, bx, chunk_ray(r, kb, ke, bx, step), acc);
         }
+    } else if (SPLIT) {
+        const int q = (Kmax - Kmin) / 4 + 1, Kw = Kmin + wave * q;
+        acc = fwd_samples_global(s, r, mu, max(klo, Kw), min(khi, Kw + q - 1));
     } else {
-        // chunk boxes too large for LDS: taps straight from the volume
-        const float xmax = NX - 1.001f, ymax = NY - 1.001f, zmax = NZ - 1.001f;
-        for (int k = klo; k <= khi; ++k) {
-            const float t = fmaf((float)(k - r.k0), step, r.f);
-            const float X = fminf(fmaxf(fmaf(t, r.dx, r.x0), 0.0f), xmax);
-            const float Y = fminf(fmaxf(fmaf(t, r.dy, r.y0), 0.0f), ymax);
-            const float Z = fminf(fmaxf(fmaf(t, r.dz, r.z0), 0.0f), zmax);
-            const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
-            const float wx = X - fx, wy = Y - fy, wz = Z - fz;
-            const int I = (int)fx, J = (int)fy, Kz = (int)fz;
-            float m[2][2][2];
-#pragma unroll
-            for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-                for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-                    for (int dx = 0; dx < 2; ++dx)
-                        m[dz][dy][dx] = mu_at(mu, s.nx, s.ny, s.nz, I + dx, J + dy, Kz + dz);
-            const float c00 = lerpf(m[0][0][0], m[0][0][1], wx);
-            const float c10 = lerpf(m[0][1][0], m[0][1][1], wx);
-            const float c01 = lerpf(m[1][0][0], m[1][0][1], wx);
-            const float c11 = lerpf(m[1][1][0], m[1][1][1], wx);
-            acc += lerpf(lerpf(c00, c10, wy), lerpf(c01, c11, wy), wz);
-        }
+        acc = fwd_samples_global(s, r, mu, klo, khi);
+    }
+    if constexpr (SPLIT) {
+        __syncthreads();  // the last chunk's readers are done
+        if (wave > 0) lds[wave * 64 + lane] = acc;
+        __syncthreads();
+        acc = ((acc + lds[64 + lane]) + lds[128 + lane]) + lds[192 + lane];
+        if (wave > 0) return;
     }
     if (active) proj[((size_t)v * s.nv + b) * s.nu + a] = acc * step;
 }
@@ -1181,7 +1257,7 @@ __device__ inline void rd_grad_tile(const GeoScalars& s, const ViewGeo* __restri
 }
 
 template <int TW, int MCH, int CAP>
-__global__ __launch_bounds__(kRdThreads) void rd_fwd_kernel(GeoScalars s,
+__global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_kernel(GeoScalars s,
                                                             const ViewGeo* __restrict__ views,
                                                             const float* __restrict__ mu,
                                                             float* __restrict__ proj)
@@ -1189,6 +1265,17 @@ __global__ __launch_bounds__(kRdThreads) void rd_fwd_kernel(GeoScalars s,
     __shared__ float lds[CAP];
     __shared__ TileShared sh;
     rd_fwd_tile<TW, MCH, CAP>(s, views, mu, proj, blockIdx.y, blockIdx.x, lds, sh);
+}
+
+template <int MCH, int CAP>
+__global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_split_kernel(GeoScalars s,
+                                                                  const ViewGeo* __restrict__ views,
+                                                                  const float* __restrict__ mu,
+                                                                  float* __restrict__ proj)
+{
+    __shared__ float lds[CAP];
+    __shared__ TileShared sh;
+    rd_fwd_tile<8, MCH, CAP, true>(s, views, mu, proj, blockIdx.y, blockIdx.x, lds, sh);
 }
 
 template <int TW, int MCH, int CAP>
@@ -1236,16 +1323,16 @@ __device__ inline int batch_problem(const RdBatch& bt)
     return p;
 }
 
-template <int TW, int MCH, int CAP>
-__global__ __launch_bounds__(kRdThreads) void rd_fwd_batch_kernel(RdBatch bt)
+template <int TW, int MCH, int CAP, bool SPLIT = false>
+__global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_batch_kernel(RdBatch bt)
 {
     __shared__ float lds[CAP];
     __shared__ TileShared sh;
     const int p = batch_problem(bt);
     const RdBatchItem& it = bt.it[p];
     const int local = (int)blockIdx.x - it.first;
-    rd_fwd_tile<TW, MCH, CAP>(it.s, it.views, it.vol, it.out, local / it.tiles,
-                              local % it.tiles, lds, sh);
+    rd_fwd_tile<TW, MCH, CAP, SPLIT>(it.s, it.views, it.vol, it.out, local / it.tiles,
+                                     local % it.tiles, lds, sh);
 }
 
 template <int TW, int MCH, int CAP>
@@ -1312,11 +1399,36 @@ static void rd_dispatch(int variant, F&& f)
     }
 }
 
+// A forward launch of few tiles under the default variant is split: a thread's
+// chain of samples is then a quarter as long and four times the compute units
+// work on it.  It repeats each ray's setup in four wavefronts and stages 8x8
+// tiles, so it loses once 16x16 tiles fill the chip.  Kernel us, 16x16 tiles
+// against split: 64 tiles (64^3, one 128^2 view) 63 / 26, 512 (64^3, 8 views)
+// 76 / 63, 576 (256^3, one 384^2 view) 116 / 82, 1024 (64^3, 16 views)
+// 107 / 108, 1024 (256^3, one 512^2 view) 122 / 114, 25600 (192^3, 100 views)
+// 2676 / 2815.
+// The chunk class (64 samples, 19.7 KB) keeps eight blocks on a compute unit;
+// (64, 6500) and (128, 9900) are no faster at 64 tiles and slower from 1024 on.
+constexpr int kRdSplitBlocks = 768, kRdSplitM = 64, kRdSplitCap = 4928;
+
+static bool rd_fwd_split(long long blocks, int variant)
+{
+    return variant == kRdDefaultVariant && blocks <= kRdSplitBlocks;
+}
+
+static int rd_split_tiles(const GeoScalars& s) { return ((s.nu + 7) / 8) * ((s.nv + 7) / 8); }
+
 void launch_rd_fwd(const GeoScalars& s, int V, const ViewGeo* views, const float* mu,
                    float* proj, int variant, hipStream_t st)
 {
     const dim3 grid(rd_tiles(s, rd_variant_shape(variant)), V);
     prof_begin(DP_K_RD_FWD, st);
+    if (rd_fwd_split((long long)grid.x * V, variant)) {
+        rd_fwd_split_kernel<kRdSplitM, kRdSplitCap>
+            <<<dim3(rd_split_tiles(s), V), kRdThreads, 0, st>>>(s, views, mu, proj);
+        prof_end(DP_K_RD_FWD, st);
+        return;
+    }
     rd_dispatch(variant, [&](auto tw, auto cl) {
         constexpr int c = decltype(cl)::value;
         rd_fwd_kernel<decltype(tw)::value, FwdClasses::mch[c], FwdClasses::cap[c]>
@@ -1361,6 +1473,19 @@ void launch_rd_fused(const GeoScalars& s, int V, const ViewGeo* views, const flo
 void launch_rd_fwd_batch(const RdBatch& bt, int blocks, int variant, hipStream_t st)
 {
     prof_begin(DP_K_RD_FWD, st);
+    if (rd_fwd_split(blocks, variant)) {
+        RdBatch sb = bt;
+        int first = 0;
+        for (int p = 0; p < bt.n; ++p) {
+            const int views = ((p + 1 < bt.n ? bt.it[p + 1].first : blocks) - bt.it[p].first) / bt.it[p].tiles;
+            sb.it[p].tiles = rd_split_tiles(bt.it[p].s);
+            sb.it[p].first = first;
+            first += sb.it[p].tiles * views;
+        }
+        rd_fwd_batch_kernel<8, kRdSplitM, kRdSplitCap, true><<<first, kRdThreads, 0, st>>>(sb);
+        prof_end(DP_K_RD_FWD, st);
+        return;
+    }
     rd_dispatch(variant, [&](auto tw, auto cl) {
         constexpr int c = decltype(cl)::value;
         rd_fwd_batch_kernel<decltype(tw)::value, FwdClasses::mch[c], FwdClasses::cap[c]>

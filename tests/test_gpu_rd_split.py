@@ -1,0 +1,49 @@
+"""Forward launches of few tiles (8x8 rays a block, each chunk of samples shared
+by its four wavefronts): ragged detectors, single pixels, chunk boxes that touch
+the grid's faces or do not fit LDS, and the last size that is split against the
+first that is not.  The bar is the existing 1e-5 of max|ref|."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from synth import Geom
+
+pytestmark = pytest.mark.gpu
+
+
+def project(dp, g, vol, angles, poses):
+    t = [torch.tensor(np.ascontiguousarray(a), dtype=d, device="cuda:0")
+         for a, d in ((angles, torch.float64), (poses, torch.float64), (vol, torch.float32))]
+    return dp.project_fwd(g, *t).cpu().numpy()
+
+
+# volume, voxel mm, detector, pixel mm, views; 768 tiles of 16x16 and 769
+@pytest.mark.parametrize("n,h,nu,nv,du,V", [
+    ((1, 1, 1), 4.0, 9, 7, 1.0, 2), ((5, 4, 3), 6.0, 1, 1, 1.0, 1), ((40, 36, 33), 1.5, 8, 9, 6.0, 1),
+    ((40, 36, 33), 1.5, 63, 65, 1.6, 3), ((41, 35, 33), 1.5, 17, 15, 4.0, 2), ((64, 64, 64), 1.0, 12, 12, 25.0, 2),
+    ((33, 64, 40), 0.3, 40, 20, 1.2, 2), ((24, 24, 24), 3.0, 48, 16, 3.0, 256), ((24, 24, 24), 3.0, 12, 9, 9.0, 769)])
+def test_small_launches(dp, oracle, n, h, nu, nv, du, V):
+    g = Geom(*n, h, 1.1 * h, 0.9 * h, nu, nv, du, du, off_u=0.5, off_v=-0.25)
+    rng = synth.rng_for(1000 + nu + V)
+    vol = rng.uniform(0, 0.05, g.vol_shape).astype(np.float32)
+    angles = rng.uniform(0, 2 * math.pi, V)
+    poses = synth.random_poses(V, 2.0, 60.0, rng)
+    ref = oracle.project_fwd(g, angles, poses, vol)
+    assert np.abs(ref).max() > 0
+    assert np.abs(project(dp, g, vol, angles, poses) - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+def test_source_inside_and_a_voxel_without_a_number(dp, oracle):
+    g = Geom(24, 24, 24, 2.0, 2.0, 2.0, 20, 18, 4.0, 4.0, sad=20.0, sdd=40.0)
+    rng = synth.rng_for(1100)
+    vol = rng.uniform(0, 0.05, g.vol_shape).astype(np.float32)
+    angles, poses = rng.uniform(0, 2 * math.pi, 2), synth.random_poses(2, 2.0, 20.0, rng)
+    ref = oracle.project_fwd(g, angles, poses, vol)
+    got = project(dp, g, vol, angles, poses)
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    vol[0, 12, 12] = np.nan
+    hit = np.isnan(project(dp, g, vol, angles, poses))
+    assert np.array_equal(hit, np.isnan(oracle.project_fwd(g, angles, poses, vol)))
