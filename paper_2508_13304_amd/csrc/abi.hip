@@ -746,7 +746,7 @@ static int run_batch(const dp_problem* pr, int32_t n, int op, void* ws, size_t w
         it.gin = op == DP_OP_FWD ? nullptr : q.grad_proj;
         it.out = op == DP_OP_FWD ? q.proj : (float*)(base + L.partials);
         it.proj = op == DP_OP_FWD_SSD ? q.proj : nullptr;
-        it.tiles = rd_tiles(s, shape);
+        it.tiles = op == DP_OP_FWD ? rd_fwd_tiles(s, var) : rd_tiles(s, shape);
         it.first = (int)blocks;
         blocks += (long long)it.tiles * q.n_views;
     }

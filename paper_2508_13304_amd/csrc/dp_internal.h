@@ -256,6 +256,30 @@ inline int rd_tiles(const GeoScalars& s, int shape)
     return ((s.nu + tw - 1) / tw) * ((s.nv + th - 1) / th);
 }
 
+// The default variant's forward splits the tiles of a small detector: a block
+// takes 8x8 rays, each chunk's samples shared by its four wavefronts.  A
+// thread's chain of samples is then a quarter as long and four times the
+// compute units work on a view; but an 8x8 tile stages more voxels per sample,
+// so many views of a larger detector are better off whole.  The rule looks at
+// one view's tiles alone, so that a view's values do not depend on what else is
+// launched with it.  Kernel us, whole against split: 64 tiles (64^3, 128^2)
+// 1 view 63 / 26, 16 views 108 / 104, 100 views 586 / 610; 144 tiles (96^3,
+// 192^2) 1 view 70 / 32, 8 views 144 / 119; 256 tiles (128^3, 256^2) 1 view
+// 68 / 39, 8 views 176 / 183, 100 views 2235 / 2531; 1024 tiles (320^3, 512^2,
+// 16 views) 1995 / 2820.  Chunks of 64 samples in the middle class's box array
+// (eight blocks on a compute unit): 32 samples take 34 us at 64 tiles.
+constexpr int kRdSplitTiles = 144, kRdSplitM = 64, kRdSplitCap = 4928;
+__host__ __device__ inline bool rd_fwd_split(const GeoScalars& s, int variant)
+{
+    return variant == kRdDefaultVariant &&
+           (long long)((s.nu + 15) / 16) * ((s.nv + 15) / 16) <= kRdSplitTiles;
+}
+// Blocks per view of the forward.
+inline int rd_fwd_tiles(const GeoScalars& s, int variant)
+{
+    return rd_fwd_split(s, variant) ? ((s.nu + 7) / 8) * ((s.nv + 7) / 8) : rd_tiles(s, rd_variant_shape(variant));
+}
+
 // Tiles of the shape with the most (per-block partial buffers are sized for it).
 inline int rd_tiles_max(const GeoScalars& s)
 {

@@ -118,6 +118,24 @@ __device__ inline RayState ray_setup(const GeoScalars& s, const ViewGeo& g, int 
     return r;
 }
 
+// A wavefront's rays through LDS: word w of lane's ray at [64 w + lane].
+constexpr int kRayWords = sizeof(RayState) / sizeof(int);
+
+__device__ inline void ray_put(const RayState& r, float* lds, int lane)
+{
+    const struct W { int w[kRayWords]; } q = __builtin_bit_cast(W, r);
+#pragma unroll
+    for (int w = 0; w < kRayWords; ++w) lds[64 * w + lane] = __int_as_float(q.w[w]);
+}
+
+__device__ inline RayState ray_get(const float* lds, int lane)
+{
+    struct W { int w[kRayWords]; } q;
+#pragma unroll
+    for (int w = 0; w < kRayWords; ++w) q.w[w] = __float_as_int(lds[64 * w + lane]);
+    return __builtin_bit_cast(RayState, q);
+}
+
 // Lane -> detector pixel: 4 wavefronts per block, each an 8x8 pixel tile,
 // in a block tile TW pixels wide (u) and 256 / TW high (v).
 template <int TW>
@@ -146,13 +164,30 @@ struct Corner {
 
 struct Box {
     int ox, oy, oz, bx, by, bz;
-    int px, py;  // LDS row and slice pitch in voxels (bx, by rounded up to odd)
+    int px, pxy;  // LDS row and slice pitch in voxels
 };
 
-// Odd LDS pitches: rays of one wavefront that sample neighbouring rows
-// (or slices) of a box then read different LDS banks; an even pitch maps
-// every other row onto the same banks.
+// LDS pitches, rounded up to odd: rays of one wavefront that sample
+// neighbouring rows (or slices) of a box then read different LDS banks; an
+// even pitch maps every other row onto the same banks.
 __device__ inline int lds_pitch(int n) { return n | 1; }
+
+// Slice pitch of a box of C floats a voxel.  The forward (one float): a
+// wavefront's 8x8 rays sample, as a rule, 8 neighbours along a row, or down
+// the rows, of 8 neighbouring slices.  The odd row pitch spreads either run
+// over 8 banks, and a slice pitch of 8 modulo 16 sets the eight runs side by
+// side over all 64, where an odd one overlaps them: 192^3, 100 views 2695 to
+// 2188 us (random angles 3596 to 2932), 256^3, 16 views 955 to 762; few tiles
+// gain nothing and lose nothing.  Boxes are planned for the odd pitch, which
+// is kept where the other does not fit.  The gradient's 16-byte voxels are read
+// a quarter wavefront at a time and lose with it (single-pass SSD of 256^3, 64
+// views 13.6 to 14.6 ms; 2, 4, 6 and 12 modulo 16: 13.65 to 15.1).
+template <int C>
+__device__ inline int slice_pitch(int px, int by, int bz, int cap)
+{
+    const int pxy = ((px * by + 7) & ~15) + 8;
+    return C == 1 && pxy * bz <= cap ? pxy : px * lds_pitch(by);
+}
 
 // Block-wide state shared by both kernels.
 struct TileShared {
@@ -244,8 +279,6 @@ __device__ inline Box chunk_box(const TileShared& sh, int K, int Ke, float step,
     Box bx;
     bx.ox = o[0]; bx.oy = o[1]; bx.oz = o[2];
     bx.bx = e[0] - o[0] + 1; bx.by = e[1] - o[1] + 1; bx.bz = e[2] - o[2] + 1;
-    bx.px = lds_pitch(bx.bx);
-    bx.py = lds_pitch(bx.by);
     return bx;
 }
 
@@ -314,14 +347,15 @@ __device__ inline void publish_box(TileShared& sh, const BoxRec& rec, int ci)
     }
 }
 
-__device__ inline Box planned_box(const TileShared& sh, int ci)
+template <int C>
+__device__ inline Box planned_box(const TileShared& sh, int ci, int cap)
 {
     const unsigned* q = sh.cur[ci & 1];
     Box b;
     b.ox = q[0] & 0xFFFF; b.oy = q[0] >> 16; b.oz = q[1] & 0xFFFF;
     b.bx = q[1] >> 16; b.by = q[2] & 0xFFFF; b.bz = q[2] >> 16;
     b.px = lds_pitch(b.bx);
-    b.py = lds_pitch(b.by);
+    b.pxy = slice_pitch<C>(b.px, b.by, b.bz, cap);
     return b;
 }
 
@@ -395,7 +429,7 @@ __device__ inline void item_load(const Box& b, const BoxItems& bi, unsigned it,
     const unsigned k0 = (unsigned)b.oz + z0 - kPadV;
     const unsigned o0 = ((k0 * (unsigned)ny + j) * (unsigned)nx + i) * 4u;
     const unsigned olast = o0 + (unsigned)(r.cnt - 1) * nxy4;
-    r.slot = (unsigned)C * ((z0 * (unsigned)b.py + ly) * (unsigned)b.px + lx);
+    r.slot = (unsigned)C * (z0 * (unsigned)b.pxy + ly * (unsigned)b.px + lx);
     if constexpr (C == 1) {
 #pragma unroll
         for (int q = 0; q < SEG; ++q) r.v[q] = ldv(mu, min(o0 + (unsigned)q * nxy4, olast));
@@ -431,7 +465,7 @@ template <int C>
 __device__ inline void item_store(const Box& b, const BoxItem<C>& r, float* dst)
 {
     constexpr int SEG = BoxItem<C>::SEG;
-    const unsigned dslot = (unsigned)(C * b.py * b.px);
+    const unsigned dslot = (unsigned)(C * b.pxy);
     unsigned slot = r.slot;
 #pragma unroll
     for (int q = 0; q < SEG; ++q, slot += dslot) {
@@ -535,9 +569,9 @@ __device__ inline void vec_item(const Box& b, const VecItems& vi, unsigned it,
     const unsigned nx4 = 4u * (unsigned)nx, nxy4 = nx4 * (unsigned)ny;
     const unsigned j = (unsigned)b.oy + ly - kPadV, k0 = (unsigned)b.oz + z0 - kPadV;
     const unsigned o0 = ((k0 * (unsigned)ny + j) * (unsigned)nx + (unsigned)gxs) * 4u;
-    const unsigned dslot = (unsigned)(C * b.py * b.px);
+    const unsigned dslot = (unsigned)(C * b.pxy);
     // LDS index of segment voxel e at the item's first z (only for 0 <= lx0 + e < bx)
-    const int slot0 = C * (((int)z0 * b.py + (int)ly) * b.px + lx0);
+    const int slot0 = C * ((int)z0 * b.pxy + (int)ly * b.px + lx0);
     // which segment voxels lie in the box (the same at every z of the item)
     bool inb[4];
 #pragma unroll
@@ -626,7 +660,7 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
 {
     constexpr int SEG = BoxItem<C>::SEG;
     const unsigned nx4 = 4u * (unsigned)nx, nxy4 = nx4 * (unsigned)ny;
-    const unsigned dslot = (unsigned)(C * b.py * b.px);
+    const unsigned dslot = (unsigned)(C * b.pxy);
     const BoxItems bi = box_items<C>(b);
     for (unsigned it = threadIdx.x; it < bi.items; it += kRdThreads) {
         const unsigned p = bi.nseg > 1 ? __umulhi(it, bi.mseg) : it;
@@ -639,7 +673,7 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
         const unsigned oc = ((unsigned)min(max(j, 0), ny - 1) * (unsigned)nx + (unsigned)min(max(i, 0), nx - 1)) * 4u;
         const auto plane = [&](int k) { return (unsigned)min(max(k, 0), nz - 1) * nxy4; };
         const auto on = [&](int k) { return col && (unsigned)k < (unsigned)nz; };
-        unsigned slot = (unsigned)C * (((unsigned)z0 * (unsigned)b.py + (unsigned)ly) * (unsigned)b.px + (unsigned)lx);
+        unsigned slot = (unsigned)C * ((unsigned)z0 * (unsigned)b.pxy + (unsigned)ly * (unsigned)b.px + (unsigned)lx);
         if constexpr (C == 1) {
             float v[SEG];
 #pragma unroll
@@ -785,15 +819,15 @@ __device__ inline ChunkRay chunk_ray(const RayState& r, int kb, int ke, const Bo
 template <int CAP>
 __device__ inline void fwd_samples(const float* lds, const Box& bx, const ChunkRay& c, float& acc)
 {
-    const int BX = bx.px, BXY = bx.px * bx.py;
-    const float fbx = (float)bx.px, fby = (float)bx.py;
+    const int BX = bx.px, BXY = bx.pxy;
+    const float fbx = (float)bx.px, fbxy = (float)bx.pxy;
     const float fimax = (float)(CAP - 1 - (BXY + BX + 1));
     // sample j of the chunk, its position measured from (X0, Y0, Z0)
     auto sample = [&](float j, float X0, float Y0, float Z0) {
         const float X = fmaf(j, c.sx, X0), Y = fmaf(j, c.sy, Y0), Z = fmaf(j, c.sz, Z0);
         const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
         const float wx = X - fx, wy = Y - fy, wz = Z - fz;
-        const int idx = lds_index(fmaf(fmaf(fz, fby, fy), fbx, fx), fimax);
+        const int idx = lds_index(fmaf(fz, fbxy, fmaf(fy, fbx, fx)), fimax);
         const float* p = lds + idx;
         const float c00 = lerpf(p[0], p[1], wx);
         const float c10 = lerpf(p[BX], p[BX + 1], wx);
@@ -867,11 +901,18 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
     }
     const bool active = a < s.nu && b < s.nv;
     const ViewGeo& g = views[v];
-    const RayState r = ray_setup(s, g, min(a, s.nu - 1), min(b, s.nv - 1));
+    // SPLIT: the first wavefront sets the rays up for all four
+    const bool own = !SPLIT || wave == 0;
+    RayState r = {};
+    if (own) {
+        r = ray_setup(s, g, min(a, s.nu - 1), min(b, s.nv - 1));
+        if (SPLIT) ray_put(r, lds, lane);
+    }
     int Kmin, Kmax;
     float margin;
-    tile_setup<SPLIT ? 8 : TW, SPLIT ? 8 : kRdThreads / TW>(s, r, active, active, a, b, a0, b0, sh, Kmin,
-                                                            Kmax, margin);
+    tile_setup<SPLIT ? 8 : TW, SPLIT ? 8 : kRdThreads / TW>(s, r, active && own, active && own, a, b, a0, b0,
+                                                            sh, Kmin, Kmax, margin);
+    if (SPLIT) r = ray_get(lds, lane);  // published by the barrier in tile_setup
     const int NX = s.nx + 2 * kPadV, NY = s.ny + 2 * kPadV, NZ = s.nz + 2 * kPadV;
     const float step = (float)s.step;
     const int klo = active ? r.klo : 1, khi = active ? r.khi : 0;
@@ -885,7 +926,7 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
         __syncthreads();
         for (int K = Kmin, ci = 0; K <= Kmax; K += M, ++ci) {
             const int Ke = min(K + M - 1, Kmax);
-            const Box bx = planned_box(sh, ci);
+            const Box bx = planned_box<1>(sh, ci, CAP);
             __syncthreads();  // the previous chunk's readers are done
             publish_box(sh, rec, ci + 1);
             load_box<1>(bx, mu, s.nx, s.ny, s.nz, lds);
@@ -1080,7 +1121,7 @@ __device__ inline void rd_grad_tile(const GeoScalars& s, const ViewGeo* __restri
         int fox = 0, foy = 0, foz = 0;  // origin of G's frame (G is zero at first)
         for (int K = Kmin, ci = 0; K <= Kmax; K += M, ++ci) {
             const int Ke = min(K + M - 1, Kmax);
-            const Box bx = planned_box(sh, ci);
+            const Box bx = planned_box<4>(sh, ci, CAP);
             G.shift((float)(fox - bx.ox), (float)(foy - bx.oy), (float)(foz - bx.oz));
             fox = bx.ox; foy = bx.oy; foz = bx.oz;
             __syncthreads();  // the previous chunk's readers are done
@@ -1089,15 +1130,15 @@ __device__ inline void rd_grad_tile(const GeoScalars& s, const ViewGeo* __restri
             __syncthreads();
             const int kb = max(K, klo), ke = min(Ke, khi);
             const ChunkRay c = chunk_ray(r, kb, ke, bx, step);
-            const int BXC = C * bx.px, BXYC = C * bx.px * bx.py;
-            const float fbx = (float)bx.px, fby = (float)bx.py;
+            const int BXC = C * bx.px, BXYC = C * bx.pxy;
+            const float fbx = (float)bx.px, fbxy = (float)bx.pxy;
             // largest base voxel whose 2x2x2 corners stay inside the box
-            const float fvmax = (float)(CAP - 2 - (bx.px * bx.py + bx.px));
+            const float fvmax = (float)(CAP - 2 - (bx.pxy + bx.px));
             // sample j of the chunk, its position measured from (X0, Y0, Z0)
             auto sample = [&](float j, float X0, float Y0, float Z0) {
                 const float X = fmaf(j, c.sx, X0), Y = fmaf(j, c.sy, Y0), Z = fmaf(j, c.sz, Z0);
                 const float fx = floorf(X), fy = floorf(Y), fz = floorf(Z);
-                const int idx = C * lds_index(fmaf(fmaf(fz, fby, fy), fbx, fx), fvmax);
+                const int idx = C * lds_index(fmaf(fz, fbxy, fmaf(fy, fbx, fx)), fvmax);
                 const float* p = lds + idx;
                 float3 q[2][2][2];
                 float m[2][2][2];
@@ -1267,15 +1308,14 @@ __global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_kernel(GeoScalars s,
     rd_fwd_tile<TW, MCH, CAP>(s, views, mu, proj, blockIdx.y, blockIdx.x, lds, sh);
 }
 
-template <int MCH, int CAP>
 __global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_split_kernel(GeoScalars s,
                                                                   const ViewGeo* __restrict__ views,
                                                                   const float* __restrict__ mu,
                                                                   float* __restrict__ proj)
 {
-    __shared__ float lds[CAP];
+    __shared__ float lds[kRdSplitCap];
     __shared__ TileShared sh;
-    rd_fwd_tile<8, MCH, CAP, true>(s, views, mu, proj, blockIdx.y, blockIdx.x, lds, sh);
+    rd_fwd_tile<8, kRdSplitM, kRdSplitCap, true>(s, views, mu, proj, blockIdx.y, blockIdx.x, lds, sh);
 }
 
 template <int TW, int MCH, int CAP>
@@ -1323,7 +1363,8 @@ __device__ inline int batch_problem(const RdBatch& bt)
     return p;
 }
 
-template <int TW, int MCH, int CAP, bool SPLIT = false>
+// SPLITS: the default variant, whose problems may be split.
+template <int TW, int MCH, int CAP, bool SPLITS>
 __global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_batch_kernel(RdBatch bt)
 {
     __shared__ float lds[CAP];
@@ -1331,8 +1372,12 @@ __global__ __launch_bounds__(kRdThreads, 8) void rd_fwd_batch_kernel(RdBatch bt)
     const int p = batch_problem(bt);
     const RdBatchItem& it = bt.it[p];
     const int local = (int)blockIdx.x - it.first;
-    rd_fwd_tile<TW, MCH, CAP, SPLIT>(it.s, it.views, it.vol, it.out, local / it.tiles,
-                                     local % it.tiles, lds, sh);
+    if (SPLITS && rd_fwd_split(it.s, kRdDefaultVariant))
+        rd_fwd_tile<8, kRdSplitM, CAP, true>(it.s, it.views, it.vol, it.out, local / it.tiles,
+                                             local % it.tiles, lds, sh);
+    else
+        rd_fwd_tile<TW, MCH, CAP>(it.s, it.views, it.vol, it.out, local / it.tiles,
+                                  local % it.tiles, lds, sh);
 }
 
 template <int TW, int MCH, int CAP>
@@ -1380,6 +1425,7 @@ struct FusedClasses {
 
 template <int N>
 using IntC = std::integral_constant<int, N>;
+static_assert(FwdClasses::cap[kRdDefaultVariant] == kRdSplitCap, "split and whole tiles of a batch share the box array");
 
 // Calls f(IntC<tile width>, IntC<chunk class>) for a variant in
 // [0, kRdVariants) (anything else: the default, 16x16 tiles and class 1).
@@ -1399,33 +1445,13 @@ static void rd_dispatch(int variant, F&& f)
     }
 }
 
-// A forward launch of few tiles under the default variant is split: a thread's
-// chain of samples is then a quarter as long and four times the compute units
-// work on it.  It repeats each ray's setup in four wavefronts and stages 8x8
-// tiles, so it loses once 16x16 tiles fill the chip.  Kernel us, 16x16 tiles
-// against split: 64 tiles (64^3, one 128^2 view) 63 / 26, 512 (64^3, 8 views)
-// 76 / 63, 576 (256^3, one 384^2 view) 116 / 82, 1024 (64^3, 16 views)
-// 107 / 108, 1024 (256^3, one 512^2 view) 122 / 114, 25600 (192^3, 100 views)
-// 2676 / 2815.
-// The chunk class (64 samples, 19.7 KB) keeps eight blocks on a compute unit;
-// (64, 6500) and (128, 9900) are no faster at 64 tiles and slower from 1024 on.
-constexpr int kRdSplitBlocks = 768, kRdSplitM = 64, kRdSplitCap = 4928;
-
-static bool rd_fwd_split(long long blocks, int variant)
-{
-    return variant == kRdDefaultVariant && blocks <= kRdSplitBlocks;
-}
-
-static int rd_split_tiles(const GeoScalars& s) { return ((s.nu + 7) / 8) * ((s.nv + 7) / 8); }
-
 void launch_rd_fwd(const GeoScalars& s, int V, const ViewGeo* views, const float* mu,
                    float* proj, int variant, hipStream_t st)
 {
-    const dim3 grid(rd_tiles(s, rd_variant_shape(variant)), V);
+    const dim3 grid(rd_fwd_tiles(s, variant), V);
     prof_begin(DP_K_RD_FWD, st);
-    if (rd_fwd_split((long long)grid.x * V, variant)) {
-        rd_fwd_split_kernel<kRdSplitM, kRdSplitCap>
-            <<<dim3(rd_split_tiles(s), V), kRdThreads, 0, st>>>(s, views, mu, proj);
+    if (rd_fwd_split(s, variant)) {
+        rd_fwd_split_kernel<<<grid, kRdThreads, 0, st>>>(s, views, mu, proj);
         prof_end(DP_K_RD_FWD, st);
         return;
     }
@@ -1473,22 +1499,10 @@ void launch_rd_fused(const GeoScalars& s, int V, const ViewGeo* views, const flo
 void launch_rd_fwd_batch(const RdBatch& bt, int blocks, int variant, hipStream_t st)
 {
     prof_begin(DP_K_RD_FWD, st);
-    if (rd_fwd_split(blocks, variant)) {
-        RdBatch sb = bt;
-        int first = 0;
-        for (int p = 0; p < bt.n; ++p) {
-            const int views = ((p + 1 < bt.n ? bt.it[p + 1].first : blocks) - bt.it[p].first) / bt.it[p].tiles;
-            sb.it[p].tiles = rd_split_tiles(bt.it[p].s);
-            sb.it[p].first = first;
-            first += sb.it[p].tiles * views;
-        }
-        rd_fwd_batch_kernel<8, kRdSplitM, kRdSplitCap, true><<<first, kRdThreads, 0, st>>>(sb);
-        prof_end(DP_K_RD_FWD, st);
-        return;
-    }
     rd_dispatch(variant, [&](auto tw, auto cl) {
         constexpr int c = decltype(cl)::value;
-        rd_fwd_batch_kernel<decltype(tw)::value, FwdClasses::mch[c], FwdClasses::cap[c]>
+        rd_fwd_batch_kernel<decltype(tw)::value, FwdClasses::mch[c], FwdClasses::cap[c],
+                            decltype(tw)::value == 16 && c == 1>
             <<<blocks, kRdThreads, 0, st>>>(bt);
     });
     prof_end(DP_K_RD_FWD, st);

@@ -1,7 +1,8 @@
-"""Forward launches of few tiles (8x8 rays a block, each chunk of samples shared
+"""The forward on small detectors (8x8 rays a block, each chunk of samples shared
 by its four wavefronts): ragged detectors, single pixels, chunk boxes that touch
-the grid's faces or do not fit LDS, and the last size that is split against the
-first that is not.  The bar is the existing 1e-5 of max|ref|."""
+the grid's faces or do not fit LDS, the last size that is split against the
+first that is not, and one view's values whatever is launched with it.  The bar
+is the existing 1e-5 of max|ref|."""
 import math
 
 import numpy as np
@@ -20,7 +21,7 @@ def project(dp, g, vol, angles, poses):
     return dp.project_fwd(g, *t).cpu().numpy()
 
 
-# volume, voxel mm, detector, pixel mm, views; 768 tiles of 16x16 and 769
+# volume, voxel mm, detector, pixel mm, views
 @pytest.mark.parametrize("n,h,nu,nv,du,V", [
     ((1, 1, 1), 4.0, 9, 7, 1.0, 2), ((5, 4, 3), 6.0, 1, 1, 1.0, 1), ((40, 36, 33), 1.5, 8, 9, 6.0, 1),
     ((40, 36, 33), 1.5, 63, 65, 1.6, 3), ((41, 35, 33), 1.5, 17, 15, 4.0, 2), ((64, 64, 64), 1.0, 12, 12, 25.0, 2),
@@ -47,3 +48,21 @@ def test_source_inside_and_a_voxel_without_a_number(dp, oracle):
     vol[0, 12, 12] = np.nan
     hit = np.isnan(project(dp, g, vol, angles, poses))
     assert np.array_equal(hit, np.isnan(oracle.project_fwd(g, angles, poses, vol)))
+
+
+
+# 144 tiles of 16x16 are split, 145 not (boxes with and without room for the wide slice pitch)
+@pytest.mark.parametrize("n,h,nu,nv,du,V", [((48, 48, 48), 2.0, 192, 192, 0.9, 2), ((37, 50, 41), 2.5, 193, 191, 0.9, 2),
+                                            ((64, 64, 20), 1.0, 2320, 9, 0.1, 2), ((48, 48, 48), 2.0, 144, 260, 1.1, 3)])
+def test_largest_split_and_smallest_whole(dp, oracle, n, h, nu, nv, du, V):
+    test_small_launches(dp, oracle, n, h, nu, nv, du, V)
+
+
+def test_a_view_does_not_depend_on_its_launch(dp):
+    g = Geom(96, 96, 96, 1.0, 1.0, 1.0, 192, 192, 0.9, 0.9)
+    rng = synth.rng_for(1200)
+    vol = synth.ellipsoid_phantom(96, 1.0, 8, rng)
+    angles, poses = rng.uniform(0, 2 * math.pi, 9), synth.random_poses(9, 5.0, 5.0, rng)
+    every = project(dp, g, vol, angles, poses)
+    for i in (0, 4, 8):
+        assert np.array_equal(project(dp, g, vol, angles[i:i + 1], poses[i:i + 1])[0], every[i])
