@@ -4,9 +4,8 @@ A 6-layer strided CNN (3x3 kernels, stride 2, channels 32-64-128-256-256-256,
 ReLU) reads a pair of DRRs -- the reference rendered at the identity pose and
 the target image -- as a 2-channel NHWC image and a linear head regresses the
 pose offset (normalised by the training range).  Every layer runs on the
-library's BF16 MFMA GEMM with FP32 accumulation (im2col, GEMM, fused
-bias/ReLU epilogue; backward via two GEMMs, col2im and a column sum); the
-parameters are kept in FP32 and rounded to BF16 for each step.  The
+library's BF16 MFMA products with FP32 accumulation (implicit im2col, fused
+bias/ReLU epilogue; backward via two implicit products); the parameters are kept in FP32 and rounded to BF16 for each step.  The
 network's proposal initialises the analytic-gradient registration, whose
 plain form (started from the identity) is the fallback.
 """
@@ -285,7 +284,7 @@ class ProposalNet:
     weights [6][F] and bias [6].  Layers with a multiple of 8 input channels
     run as implicit GEMMs (operand tiles gathered from the activations, no
     im2col matrix; the input gradient per parity class of input pixels, no
-    col2im), the 2-channel input layer through an explicit im2col.  The
+    col2im), the 2-channel input layer as one gathered product step.  The
     forward product reads the BF16 weights with the FP32 bias in its
     epilogue; the weight-gradient product (with an implicit or explicit ones
     column) writes the layer's weight and bias gradients straight into its
