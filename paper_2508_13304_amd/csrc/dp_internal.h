@@ -268,7 +268,7 @@ inline int rd_tiles(const GeoScalars& s, int shape)
 // 68 / 39, 8 views 176 / 183, 100 views 2235 / 2531; 1024 tiles (320^3, 512^2,
 // 16 views) 1995 / 2820.  Chunks of 64 samples in the middle class's box array
 // (eight blocks on a compute unit): 32 samples take 34 us at 64 tiles.
-constexpr int kRdSplitTiles = 144, kRdSplitM = 64, kRdSplitCap = 4928;
+constexpr int kRdSplitTiles = 144, kRdSplitM = 64, kRdSplitCap = 5064;
 __host__ __device__ inline bool rd_fwd_split(const GeoScalars& s, int variant)
 {
     return variant == kRdDefaultVariant &&

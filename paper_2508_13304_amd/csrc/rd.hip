@@ -177,16 +177,16 @@ __device__ inline int lds_pitch(int n) { return n | 1; }
 // the rows, of 8 neighbouring slices.  The odd row pitch spreads either run
 // over 8 banks, and a slice pitch of 8 modulo 16 sets the eight runs side by
 // side over all 64, where an odd one overlaps them: 192^3, 100 views 2695 to
-// 2188 us (random angles 3596 to 2932), 256^3, 16 views 955 to 762; few tiles
-// gain nothing and lose nothing.  Boxes are planned for the odd pitch, which
-// is kept where the other does not fit.  The gradient's 16-byte voxels are read
-// a quarter wavefront at a time and lose with it (single-pass SSD of 256^3, 64
+// 2157 us (random angles 3596 to 2930), 256^3, 16 views 955 to 754; few tiles
+// gain nothing and lose nothing.  The gradient's 16-byte voxels are read a
+// quarter wavefront at a time and lose with it (single-pass SSD of 256^3, 64
 // views 13.6 to 14.6 ms; 2, 4, 6 and 12 modulo 16: 13.65 to 15.1).
 template <int C>
-__device__ inline int slice_pitch(int px, int by, int bz, int cap)
+__device__ inline int slice_pitch(int px, int by)
 {
-    const int pxy = ((px * by + 7) & ~15) + 8;
-    return C == 1 && pxy * bz <= cap ? pxy : px * lds_pitch(by);
+    // unsigned: a box too large for any array wraps (and is refused by its rows)
+    const unsigned n = (unsigned)px * (unsigned)by;
+    return (int)(C == 1 ? ((n + 7) & ~15u) + 8 : (unsigned)px * (unsigned)lds_pitch(by));
 }
 
 // Block-wide state shared by both kernels.
@@ -292,6 +292,7 @@ __device__ inline Box chunk_box(const TileShared& sh, int K, int Ke, float step,
 // orbit views: 3.69 to 3.62 ms with it; single-pass SSD of 256^3, 64 views:
 // 13.94 to 13.77).
 // Thread i < the chunk count leaves the record of chunk i in `rec`.
+template <int C>
 __device__ inline int plan_chunks(TileShared& sh, int Kmin, int Kmax, int Mmax, int cap,
                                   float step, float margin, int NX, int NY, int NZ, BoxRec& rec)
 {
@@ -309,7 +310,9 @@ __device__ inline int plan_chunks(TileShared& sh, int Kmin, int Kmax, int Mmax, 
                 asm volatile("" ::: "memory");  // corner reads stay in the loop: registers are short here
                 const int K = Kmin + c * Mw;
                 const Box b = chunk_box(sh, K, min(K + Mw - 1, Kmax), step, margin, NX, NY, NZ);
-                over = over || (float)lds_pitch(b.bx) * (float)lds_pitch(b.by) * (float)b.bz > (float)cap;
+                const int px = lds_pitch(b.bx);
+                over = over || (float)px * (float)b.by > (float)cap ||
+                       (float)slice_pitch<C>(px, b.by) * (float)b.bz > (float)cap;
             }
         // fits: the length; shorten further: -1; no length will do: 0
         const bool fits = nch <= kMaxChunks && __builtin_amdgcn_ballot_w64(over) == 0;
@@ -348,14 +351,14 @@ __device__ inline void publish_box(TileShared& sh, const BoxRec& rec, int ci)
 }
 
 template <int C>
-__device__ inline Box planned_box(const TileShared& sh, int ci, int cap)
+__device__ inline Box planned_box(const TileShared& sh, int ci)
 {
     const unsigned* q = sh.cur[ci & 1];
     Box b;
     b.ox = q[0] & 0xFFFF; b.oy = q[0] >> 16; b.oz = q[1] & 0xFFFF;
     b.bx = q[1] >> 16; b.by = q[2] & 0xFFFF; b.bz = q[2] >> 16;
     b.px = lds_pitch(b.bx);
-    b.pxy = slice_pitch<C>(b.px, b.by, b.bz, cap);
+    b.pxy = slice_pitch<C>(b.px, b.by);
     return b;
 }
 
@@ -918,7 +921,7 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
     const int klo = active ? r.klo : 1, khi = active ? r.khi : 0;
     float acc = 0.0f;
     BoxRec rec = {};
-    const int M = Kmin <= Kmax ? plan_chunks(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
+    const int M = Kmin <= Kmax ? plan_chunks<1>(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
                                              rec)
                                : 1;
     if (M > 0) {
@@ -926,7 +929,7 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
         __syncthreads();
         for (int K = Kmin, ci = 0; K <= Kmax; K += M, ++ci) {
             const int Ke = min(K + M - 1, Kmax);
-            const Box bx = planned_box<1>(sh, ci, CAP);
+            const Box bx = planned_box<1>(sh, ci);
             __syncthreads();  // the previous chunk's readers are done
             publish_box(sh, rec, ci + 1);
             load_box<1>(bx, mu, s.nx, s.ny, s.nz, lds);
@@ -1109,7 +1112,7 @@ __device__ inline void rd_grad_tile(const GeoScalars& s, const ViewGeo* __restri
     const int klo = active ? r.klo : 1, khi = active ? r.khi : 0;
     GradAcc G;
     BoxRec rec = {};
-    const int M = Kmin <= Kmax ? plan_chunks(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
+    const int M = Kmin <= Kmax ? plan_chunks<C>(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
                                              rec)
                                : 1;
     if (M > 0) {
@@ -1121,7 +1124,7 @@ __device__ inline void rd_grad_tile(const GeoScalars& s, const ViewGeo* __restri
         int fox = 0, foy = 0, foz = 0;  // origin of G's frame (G is zero at first)
         for (int K = Kmin, ci = 0; K <= Kmax; K += M, ++ci) {
             const int Ke = min(K + M - 1, Kmax);
-            const Box bx = planned_box<4>(sh, ci, CAP);
+            const Box bx = planned_box<C>(sh, ci);
             G.shift((float)(fox - bx.ox), (float)(foy - bx.oy), (float)(foz - bx.oz));
             fox = bx.ox; foy = bx.oy; foz = bx.oz;
             __syncthreads();  // the previous chunk's readers are done
@@ -1407,14 +1410,17 @@ __global__ __launch_bounds__(kRdThreads, 4) void rd_fused_batch_kernel(RdBatch b
 }
 
 // Chunk classes (chunk length before adaptation, LDS voxels) per kernel kind:
-//   forward : (16, 4096) (32, 4928) (64, 12288)  (middle class: 19.9 KB, eight blocks per CU)
+//   forward : (16, 4096) (32, 5064) (64, 12288)  (middle class: 20,456 bytes, the most of
+//             which eight blocks fit a compute unit; kernel us at 4928, 5064, 5790, 6760:
+//             192^3, 100 views of random poses 2787, 2547, 2508, 2531, around the orbit
+//             3385, 3346, 3385, 3266; 256^3, 64 views of 512^2 4316, 4379, 4443, 4704)
 //   gradient: ( 8, 2048) (16, 2520) (32, 4096)
 //   fused   : ( 8, 2048) (16, 2520) (32, 4096)  (both: four channels per voxel)
 // The fused and gradient kernels' first two classes take at most 40,520
 // bytes of LDS per block, which measures as four blocks (16 wavefronts) per
 // compute unit (40,904 bytes measures as three); the third runs two.
 struct FwdClasses {
-    static constexpr int mch[3] = {16, 32, 64}, cap[3] = {4096, 4928, 12288};
+    static constexpr int mch[3] = {16, 32, 64}, cap[3] = {4096, kRdSplitCap, 12288};
 };
 struct GradClasses {
     static constexpr int mch[3] = {8, 16, 32}, cap[3] = {2048, 2520, 4096};
@@ -1425,7 +1431,6 @@ struct FusedClasses {
 
 template <int N>
 using IntC = std::integral_constant<int, N>;
-static_assert(FwdClasses::cap[kRdDefaultVariant] == kRdSplitCap, "split and whole tiles of a batch share the box array");
 
 // Calls f(IntC<tile width>, IntC<chunk class>) for a variant in
 // [0, kRdVariants) (anything else: the default, 16x16 tiles and class 1).
