@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "dp_internal.h"
+#include "gemm_plan.h"
 
 namespace dp {
 
@@ -124,12 +125,6 @@ __device__ inline uint4 load8(__amdgpu_buffer_rsrc_t r, unsigned off)
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
-// How a dense operand's chunks are loaded: element by element (any alignment);
-// 16 bytes at a time with guarded element loads at ragged edges (ld a multiple
-// of 8 and the matrix 16-byte aligned); or always 16 bytes at a time (no
-// chunk straddles the end of k or of the rows either).
-enum Vec { kElems, kRagged, kWhole };
-
 // A dense BF16 matrix (k-contiguous if KC).
 template <bool KC_, Vec VEC>
 struct DenseSrc {
@@ -146,7 +141,9 @@ struct DenseSrc {
 #pragma unroll
         for (int u = 0; u < R / 32; ++u) {
             const int r = Chunk<KC, R>::row(tid, u), k = Chunk<KC, R>::k(tid, u);
-            st.off[u] = row0 + r < rows ? 2u * (unsigned)(KC ? r * ld + k : k * ld + r) : kOut;
+            // (read for kWhole only: ld < kWholeLd there, or the operand has less than 2^31 elements)
+            st.off[u] = row0 + r < rows ? 2u * (KC ? (unsigned)r * (unsigned)ld + (unsigned)k : (unsigned)k * (unsigned)ld + (unsigned)r)
+                                        : kOut;
         }
         return st;
     }
@@ -863,13 +860,6 @@ static void run_gemm_f32(int M, int N, int K, const AS& as, const BS& bs, float*
     }
 }
 
-// Whether a dense operand of `rows` rows and K columns can take 16-byte loads.
-static Vec dense_vec(bool kc, int rows, int K, int ld, const void* P)
-{
-    if (ld % 8 != 0 || ((uintptr_t)P & 15) != 0) return kElems;
-    return (kc ? K : rows) % 8 == 0 ? kWhole : kRagged;
-}
-
 // Dense operands: A stored [M][K] unless ta ([K][M]), B stored [K][N] unless
 // tb ([N][K]).
 template <Vec VEC, class F>
@@ -891,7 +881,7 @@ void launch_gemm_bf16(bool ta, bool tb, int M, int N, int K, const void* A, int 
     auto go = [&](const auto& as, const auto& bs) {
         run_gemm_f32(M, N, K, as, bs, C, ldc, accumulate, ws, ws_bytes, st);
     };
-    const Vec v = std::min(dense_vec(!ta, M, K, lda, A), dense_vec(tb, N, K, ldb, B));
+    const Vec v = std::min(dense_vec(!ta, M, K, lda, (uintptr_t)A), dense_vec(tb, N, K, ldb, (uintptr_t)B));
     if (v == kWhole) with_dense<kWhole>(ta, tb, a, lda, M, b, ldb, N, go);
     else if (v == kRagged) with_dense<kRagged>(ta, tb, a, lda, M, b, ldb, N, go);
     else with_dense<kElems>(ta, tb, a, lda, M, b, ldb, N, go);
@@ -906,7 +896,7 @@ void launch_gemm_bias_act(int M, int N, int K, const void* A, int lda, const voi
     const __bf16* a = (const __bf16*)A;
     const __bf16* b = (const __bf16*)B;
     const auto go = [&](const auto& as, const auto& bs) { launch_gemm(M, N, K, 1, as, bs, ep, st); };
-    const Vec v = std::min(dense_vec(true, M, K, lda, A), dense_vec(true, N, K, ldb, B));
+    const Vec v = std::min(dense_vec(true, M, K, lda, (uintptr_t)A), dense_vec(true, N, K, ldb, (uintptr_t)B));
     if (v == kWhole) go(DenseSrc<true, kWhole>{a, lda, M}, DenseSrc<true, kWhole>{b, ldb, N});
     else if (v == kRagged) go(DenseSrc<true, kRagged>{a, lda, M}, DenseSrc<true, kRagged>{b, ldb, N});
     else go(DenseSrc<true, kElems>{a, lda, M}, DenseSrc<true, kElems>{b, ldb, N});

@@ -82,3 +82,22 @@ def test_two_channel_input_off_its_alignment(dp):
     flat = torch.zeros(x.numel() + 1, dtype=torch.bfloat16, device="cuda")
     flat[1:] = x.reshape(-1)
     assert torch.equal(net.forward(flat[1:].view(x.shape)), net.forward(x))
+
+
+@pytest.mark.parametrize("ta", [False, True])
+def test_rows_further_apart_than_32_bit_offsets_reach(dp, ta):
+    """64 rows (or k) of 2^25 + 8 elements: the last one lies past 2^32 bytes."""
+    from paper_2508_13304_amd import proposal as pr
+    g = torch.Generator("cuda").manual_seed(11)
+    ld = 2 ** 25 + 8
+    big = torch.empty((72, ld), dtype=torch.bfloat16, device="cuda")
+    a = big[:, :64]
+    a.copy_(torch.randn((72, 64), device="cuda", generator=g))
+    b = torch.randn((64 if not ta else 72, 40), device="cuda", generator=g).bfloat16()
+    A = a.double().T if ta else a.double()
+    assert ((pr.gemm(a, b, ta=ta).double() - A @ b.double()).abs() <= 1e-5 * (A.abs() @ b.double().abs())).all()
+    if not ta:
+        bias = torch.randn(40, device="cuda", generator=g)
+        ref, mag = (A @ b.double() + bias).relu(), A.abs() @ b.double().abs() + bias.abs()
+        y = pr.gemm_bias_act(a, b.T.contiguous(), 64, bias).double()
+        assert ((y - ref).abs() <= ref / 256 + 1e-5 * mag).all()
