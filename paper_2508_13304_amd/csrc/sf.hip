@@ -664,6 +664,7 @@ __device__ inline void sf_walk(const SfColumn& col, const ViewGeo& g, const GeoS
 // cannot meet in a pixel then, and LDS operations of a wavefront are carried
 // out in order.  Lanes that do start in the same column (voxels narrower than a pixel)
 // take turns.
+// Voxels with wider windows, and those that hold no number, go to memory pixel by pixel.
 // FP32 atomics are what this avoids: straight to memory, one per pixel of
 // every footprint, they took most of the kernel's time, and LDS ones take
 // about 110 cycles per wavefront (measured: ds_add_f32, no conflicts).
@@ -740,7 +741,9 @@ __device__ inline void sf_scatter(const SfColumn& c, const GeoScalars& s, int do
         // window, not clipped: first column and row relative to the bases
         const int ra = sf_floor(x.t[0] - 0.5f) + 1, rb = sf_floor(x.blo - 0.5f) + 1;
         const float xs = (float)ra - 0.5f, ys = (float)rb - 0.5f;
-        const bool fits = ta <= xs + (0.5f + 4 * kSfQuads) && tb <= ys + (0.5f + 3 * kSfQuads);
+        // (a patch also adds to pixels of weight zero, where inf and NaN must not go)
+        const bool fits = ta <= xs + (0.5f + 4 * kSfQuads) && tb <= ys + (0.5f + 3 * kSfQuads) &&
+                          fabsf(scale) < INFINITY;
         // lanes `turns` apart start in different columns
         const int pa = c.abase + ra;
         int turns = 1;

@@ -69,3 +69,30 @@ def test_pixel_without_a_number_reaches_its_voxels_only(dp, oracle, kind, value)
     assert np.mean(np.isfinite(got[away])) > 0.999 and not np.isfinite(got[hit]).any()
     ok = away & np.isfinite(got)
     np.testing.assert_array_equal(got[ok], clean[ok])
+
+
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+@pytest.mark.parametrize("kind", ["sf", "dd"])
+@pytest.mark.parametrize("name", ["one-quad", "quads"])
+def test_voxel_without_a_number_reaches_its_pixels_only(dp, oracle, name, kind, value):
+    g = CASES[name]
+    rng = synth.rng_for(790)
+    angles, poses = np.array([0.4, 2.0]), synth.random_poses(2, 1.0, 4.0, rng)
+    vol = rng.uniform(0.0, 0.05, g.vol_shape).astype(np.float32)
+    at = (g.nz // 2, g.ny // 2 - 1, g.nx // 2 + 1)
+    vol[at] = 0.0
+    clean = dp.fp_project(g, f64(angles), f64(poses), f32(vol), kind).cpu().numpy()
+    vol[at] = value
+    got = dp.fp_project(g, f64(angles), f64(poses), f32(vol), kind).cpu().numpy()
+    ind = np.zeros_like(vol)
+    ind[at] = 1.0
+    w = oracle.fp_project(g, angles, poses, ind, kind)
+    away, hit = w == 0.0, w > 1e-4 * w.max()
+    assert hit.sum() >= 2
+    # a footprint that ends within rounding of a pixel's edge may touch that pixel
+    rim = away & ~np.isfinite(got)
+    assert rim.sum() <= 2
+    assert (np.isnan(got[hit]) if math.isnan(value) else got[hit] == value).all()
+    ok = away & ~rim
+    # (FP32 atomics: the last bits depend on the order of the sums)
+    assert np.abs(got[ok] - clean[ok]).max() <= 1e-5 * np.abs(clean).max()
