@@ -101,3 +101,26 @@ def test_rows_further_apart_than_32_bit_offsets_reach(dp, ta):
         ref, mag = (A @ b.double() + bias).relu(), A.abs() @ b.double().abs() + bias.abs()
         y = pr.gemm_bias_act(a, b.T.contiguous(), 64, bias).double()
         assert ((y - ref).abs() <= ref / 256 + 1e-5 * mag).all()
+
+
+def test_more_than_2_to_the_24_rows(dp):
+    """Rows past 2^24 of an image one pixel wide, with no numbers behind its end: the
+    part of the last step beyond K = 72 reads nothing."""
+    from paper_2508_13304_amd import proposal as pr
+    g = torch.Generator("cuda").manual_seed(12)
+    h, n = 2 ** 24 + 40, 300
+    buf = torch.full((h + 64, 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf[:h] = 0
+    buf[h - n:h] = torch.randn((n, 8), device="cuda", generator=g)
+    x = buf[:h].view(1, h, 1, 8)
+    w, b = (0.1 * torch.randn((8, 80), device="cuda", generator=g)).bfloat16(), torch.zeros(8, device="cuda")
+    X, W = x[:, h - n:].double(), w[:, :72].double()
+    col = im2col(X, 1)[2:]
+    ref, mag = col @ W.T, col.abs() @ W.abs().T
+    y = pr.conv_fwd(x, w, 1, b, relu=False)
+    assert ((y[0, h - n + 2:, 0].double() - ref).abs() <= ref.abs() / 256 + 1e-5 * mag).all()
+    assert (y[0, :h - n - 1] == 0).all()
+    ref, mag = col2im(X.reshape(-1, 8) @ W, X.shape, 1), col2im(X.reshape(-1, 8).abs() @ W.abs(), X.shape, 1)
+    dx = pr.conv_dgrad_act(x, w, (1, h, 1, 8), 1)
+    d = (dx[:, h - n:].double() - ref).abs() - (ref.abs() / 256 + 1e-5 * mag)
+    assert (d[:, 2:] <= 0).all() and (dx[0, :h - n - 1] == 0).all()
