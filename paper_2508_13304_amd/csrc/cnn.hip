@@ -601,25 +601,7 @@ __device__ inline void gemm_tile(int M, int N, int z, int m0, int n0, int kbeg, 
     }
 }
 
-// The blocks of a launch come in groups that share operands (the column tiles
-// of a row tile; all tiles of a split-K range), and consecutive blocks go to
-// the eight XCDs in turn, each with its own L2.  So group and member are taken
-// from the block number such that a group stays on one XCD, and neighbouring
-// groups (whose convolution windows overlap) do too.
-struct Groups {
-    int count, size, per;  // groups, blocks per group, groups per XCD
-    Groups(int c, int s) : count(c), size(s), per((c + 7) / 8) {}
-    unsigned blocks() const { return 8u * (unsigned)per * (unsigned)size; }
-    // pass: which of several passes over all groups this block belongs to
-    __device__ bool get(int& group, int& member, int pass = 0) const
-    {
-        const unsigned xcd = blockIdx.x & 7u, j = (blockIdx.x >> 3) - (unsigned)(pass * per * size);
-        member = (int)(j % (unsigned)size);
-        const int g = (int)(j / (unsigned)size);
-        group = (int)xcd * per + g;
-        return group < count;
-    }
-};
+__device__ inline unsigned block_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
 // With splits > 1 (split-K) each split covers its own contiguous k range.
 template <int BM, int BN, class AS, class BS, class EP>
@@ -627,7 +609,7 @@ __global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 3 : 4) void gemm_kernel
                                                                                 int splits, AS as, BS bs, EP ep)
 {
     int g, t, tm, tn, z = 0;
-    if (!gr.get(g, t)) return;
+    if (!gr.get(block_id(), g, t)) return;
     if (splits > 1) {
         const int nt = (N + BN - 1) / BN, parts = gr.count / splits;
         z = g / parts;
@@ -660,12 +642,12 @@ __global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 3 : 4) void dgrad_kerne
     int g, tn, cls;
     if (mixed) {
         int t;
-        if (!gr.get(g, t)) return;
+        if (!gr.get(blockIdx.x, g, t)) return;
         tn = t / mixed;
         cls = t - tn * mixed;
     } else {
         cls = (int)((blockIdx.x >> 3) / (unsigned)(gr.per * gr.size));
-        if (!gr.get(g, tn, cls)) return;
+        if (!gr.get(blockIdx.x, g, tn, cls)) return;
     }
     const DgradClass& c = all.c[cls];
     const int m0 = g * BM;
@@ -705,7 +687,8 @@ static void launch_gemm(int M, int N, int K, int z, const AS& as, const BS& bs, 
         int parts = 1;
         while ((z * parts + 7) / 8 * 8 > 1.05 * z * parts) parts *= 2;
         const Groups gr = z > 1 ? Groups(z * parts, (tm * tn + parts - 1) / parts) : Groups(tm, tn);
-        gemm_kernel<BM, BN><<<gr.blocks(), 256, 0, st>>>(M, N, K, gr, z, as, bs, ep);
+        const Grid grid = gemm_grid(gr.blocks());
+        gemm_kernel<BM, BN><<<dim3(grid.x, grid.y), 256, 0, st>>>(M, N, K, gr, z, as, bs, ep);
     };
     // (operands with guarded loads: the loads are what takes the time)
     if constexpr (AS::kGuarded || BS::kGuarded)
@@ -987,7 +970,7 @@ void launch_conv_dgrad_act(int N, int H, int W, int Ci, int Co, int s, const voi
             std::sort(all.c, all.c + n, [](const DgradClass& a, const DgradClass& b) {
                 return a.nky * a.nkx > b.nky * b.nkx;
             });
-            dgrad_kernel<BM, BN><<<gr.blocks() * (mixed ? 1 : n), 256, 0, st>>>(
+            dgrad_kernel<BM, BN><<<(unsigned)gr.blocks() * (mixed ? 1 : n), 256, 0, st>>>(
                 g, all, gr, mixed, (const __bf16*)dz, (const __bf16*)w, ldw, (const __bf16*)y, relu ? 1 : 0, (__bf16*)out);
         });
         n = most = 0;

@@ -1,7 +1,13 @@
-// Host rules of the GEMM launches (plain C++: no device code).
+// Rules of the GEMM launches (plain C++, the block order also on the device).
 #pragma once
 
 #include <stdint.h>
+
+#ifdef __HIPCC__
+#define DP_HD __host__ __device__
+#else
+#define DP_HD
+#endif
 
 namespace dp {
 
@@ -23,6 +29,37 @@ inline Vec dense_vec(bool kc, int rows, int K, int ld, uintptr_t P)
 {
     if (ld % 8 != 0 || (P & 15) != 0) return kElems;
     return (kc ? K : rows) % 8 == 0 && ld < kWholeLd ? kWhole : kRagged;
+}
+
+// The blocks of a launch come in groups that share operands (the column tiles
+// of a row tile; all tiles of a split-K range), and consecutive blocks go to
+// the eight XCDs in turn, each with its own L2.  So group and member are taken
+// from the block number such that a group stays on one XCD, and neighbouring
+// groups (whose convolution windows overlap) do too.
+struct Groups {
+    int count, size, per;  // groups, blocks per group, groups per XCD
+    Groups(int c, int s) : count(c), size(s), per((c + 7) / 8) {}
+    uint64_t blocks() const { return 8ull * (unsigned)per * (unsigned)size; }
+    // pass: which of several passes over all groups this block belongs to
+    DP_HD bool get(unsigned block, int& group, int& member, int pass = 0) const
+    {
+        const unsigned xcd = block & 7u, j = (block >> 3) - (unsigned)pass * (unsigned)per * (unsigned)size;
+        const unsigned g = j / (unsigned)size;
+        member = (int)(j - g * (unsigned)size);
+        group = (int)(xcd * (unsigned)per + g);
+        return g < (unsigned)per && group < count;
+    }
+};
+
+// Grid of so many blocks of 256 threads (block = y * grid.x + x; blocks beyond the
+// number do nothing): a launch takes less than 2^32 threads along x.
+struct Grid {
+    unsigned x, y;
+};
+inline Grid gemm_grid(uint64_t blocks)
+{
+    constexpr uint64_t row = 1u << 22;  // a multiple of the XCDs' eight
+    return blocks <= row ? Grid{(unsigned)blocks, 1u} : Grid{(unsigned)row, (unsigned)((blocks + row - 1) / row)};
 }
 
 }  // namespace dp

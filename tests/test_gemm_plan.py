@@ -10,7 +10,7 @@ CSRC = os.path.join(ROOT, "paper_2508_13304_amd", "csrc")
 
 def run(tmp_path, body):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
-    src.write_text('#include <cstdio>\n#include <climits>\n#include "gemm_plan.h"\nusing namespace dp;\n'
+    src.write_text('#include <cstdio>\n#include <climits>\n#include <vector>\n#include "gemm_plan.h"\nusing namespace dp;\n'
                    "int main()\n{\n" + body + "\nreturn 0;\n}\n")
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)],
                    check=True)
@@ -39,3 +39,31 @@ def test_operands_with_32_bit_offsets_are_in_their_range(tmp_path):
     (0, 60, 5, 64, 4096, "kRagged"), (1, 64, 64, 65, 4096, "kElems"), (1, 64, 64, 64, 4098, "kElems")])
 def test_operand_forms(tmp_path, kc, rows, k, ld, ptr, want):
     run(tmp_path, f"return dense_vec({kc}, {rows}, {k}, {ld}, {ptr}) != {want};")
+
+
+def test_every_tile_of_a_launch_is_one_block(tmp_path):
+    """Including products with more blocks than a launch takes along x."""
+    run(tmp_path, r"""
+    const long long sizes[][2] = {{1, 1}, {1, 256}, {7, 3}, {8, 1}, {9, 4}, {1025, 2}, {1 << 23, 2}, {(1 << 23) + 1, 3}};
+    for (auto& s : sizes) {
+        const Groups gr((int)s[0], (int)s[1]);
+        const Grid grid = gemm_grid(gr.blocks());
+        if ((uint64_t)grid.x * 256 >= 1ull << 32 || grid.y > 65535 || (uint64_t)grid.x * grid.y < gr.blocks()) {
+            printf("grid %u x %u\n", grid.x, grid.y);
+            return 1;
+        }
+        std::vector<bool> seen(s[0] * s[1]);
+        uint64_t n = 0;
+        for (uint64_t b = 0; b < (uint64_t)grid.x * grid.y; ++b) {
+            int g, m;
+            if (!gr.get((unsigned)b, g, m)) continue;
+            if (g < 0 || g >= s[0] || m < 0 || m >= s[1] || seen[g * s[1] + m]) {
+                printf("%lld x %lld: block %llu\n", s[0], s[1], (unsigned long long)b);
+                return 1;
+            }
+            seen[g * s[1] + m] = true;
+            ++n;
+        }
+        if (n != (uint64_t)(s[0] * s[1])) { printf("%lld x %lld: %llu tiles\n", s[0], s[1], (unsigned long long)n); return 1; }
+    }
+    """)
