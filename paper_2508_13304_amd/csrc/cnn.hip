@@ -470,7 +470,12 @@ struct EpBiasAct {
             *(uint4*)p = v.u;
             return;
         }
-        for (int q = 0; q < 8 && n + q < N; ++q) p[q] = v.h[q];
+        // unrolled: an array indexed at run time lives in LDS or scratch, and the
+        // LDS form reads its place from the dispatch packet in host memory, which
+        // cost every launch of enough blocks about 10 us
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (n + q < N) p[q] = v.h[q];
     }
 };
 
