@@ -610,22 +610,11 @@ __device__ inline unsigned block_id() { return blockIdx.y * gridDim.x + blockIdx
 
 // With splits > 1 (split-K) each split covers its own contiguous k range.
 template <int BM, int BN, class AS, class BS, class EP>
-__global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 3 : 4) void gemm_kernel(int M, int N, int K, Groups gr,
+__global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 3 : 4) void gemm_kernel(int M, int N, int K, TileMap map,
                                                                                 int splits, AS as, BS bs, EP ep)
 {
-    int g, t, tm, tn, z = 0;
-    if (!gr.get(block_id(), g, t)) return;
-    if (splits > 1) {
-        const int nt = (N + BN - 1) / BN, parts = gr.count / splits;
-        z = g / parts;
-        t += (g - z * parts) * gr.size;  // a split's tiles come in equal parts
-        tm = t / nt;
-        tn = t - tm * nt;
-        if (tm * BM >= M) return;
-    } else {
-        tm = g;
-        tn = t;
-    }
+    int tm, tn, z;
+    if (!map.get(block_id(), tm, tn, z)) return;
     const int ksplit = (K + splits - 1) / splits, per = (ksplit + 31) / 32 * 32;
     const int kbeg = z * per, kend = min(K, kbeg + per);
     gemm_tile<BM, BN>(M, N, z, tm * BM, tn * BN, kbeg, kend, as, bs, ep);
@@ -666,6 +655,8 @@ __global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 3 : 4) void dgrad_kerne
 // kernels; with half as many blocks asked for 3 % more, twice as many 2 % more),
 // split reductions, whose blocks only read and multiply, four (1.66 / 1.60 / 1.58 ms
 // with one / two / four).
+// Products of at most 32 columns never take a tile of 64 (43264 x 8 x 72: 6.5 us with
+// 64x64, 5.4 with 64x32).
 constexpr long long kMinBlocks = 512;
 template <class F>
 static void with_tile(long long M, long long N, long long z, F&& f, long long least = kMinBlocks)
@@ -674,8 +665,8 @@ static void with_tile(long long M, long long N, long long z, F&& f, long long le
     typedef std::integral_constant<int, 32> I32;
     typedef std::integral_constant<int, 64> I64;
     typedef std::integral_constant<int, 128> I128;
-    if (N <= 32 && M <= 64) f(I64(), I32());
-    else if (N <= 32 && blocks(128, 32) >= least) f(I128(), I32());
+    if (N <= 32 && M > 64 && blocks(128, 32) >= least) f(I128(), I32());
+    else if (N <= 32) f(I64(), I32());
     else if (M > 64 && N > 64 && blocks(128, 128) >= least) f(I128(), I128());
     else if (M > 64 && N > 32 && blocks(128, 64) >= least) f(I128(), I64());
     else f(I64(), I64());
@@ -686,14 +677,9 @@ static void launch_gemm(int M, int N, int K, int z, const AS& as, const BS& bs, 
 {
     const auto go = [&](auto bm, auto bn) {
         constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
-        const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-        // the tiles of a split in as many parts as it takes for the XCDs to get
-        // about the same number of them (within 5 %)
-        int parts = 1;
-        while ((z * parts + 7) / 8 * 8 > 1.05 * z * parts) parts *= 2;
-        const Groups gr = z > 1 ? Groups(z * parts, (tm * tn + parts - 1) / parts) : Groups(tm, tn);
-        const Grid grid = gemm_grid(gr.blocks());
-        gemm_kernel<BM, BN><<<dim3(grid.x, grid.y), 256, 0, st>>>(M, N, K, gr, z, as, bs, ep);
+        const TileMap map((M + BM - 1) / BM, (N + BN - 1) / BN, z);
+        const Grid grid = gemm_grid(map.gr.blocks());
+        gemm_kernel<BM, BN><<<dim3(grid.x, grid.y), 256, 0, st>>>(M, N, K, map, z, as, bs, ep);
     };
     // (operands with guarded loads: the loads are what takes the time)
     if constexpr (AS::kGuarded || BS::kGuarded)

@@ -62,4 +62,41 @@ inline Grid gemm_grid(uint64_t blocks)
     return blocks <= row ? Grid{(unsigned)blocks, 1u} : Grid{(unsigned)row, (unsigned)((blocks + row - 1) / row)};
 }
 
+// The tm x tn tiles of a product's z split-K ranges as blocks.  A group holds the
+// column tiles of a row tile (z = 1) or all tiles of a range, in as many equal
+// parts as it takes for the XCDs to get about the same number of groups (within
+// 5 %): 24 x 40000 x 64, whose one row tile kept seven XCDs idle, 15 us whole and
+// 5 in parts.
+struct TileMap {
+    Groups gr;
+    int parts, tn, tiles;  // tiles of an undivided group
+    bool split;
+    static int parts_of(int units, int tiles)
+    {
+        int p = 1;
+        while (p < tiles && (units * (int64_t)p + 7) / 8 * 8 > 1.05 * units * (double)p) p *= 2;
+        return p;
+    }
+    TileMap(int tm, int tn_, int z)
+        : gr(1, 1), parts(1), tn(tn_), tiles(z > 1 ? tm * tn_ : tn_), split(z > 1)
+    {
+        const int units = z > 1 ? z : tm;
+        parts = parts_of(units, tiles);
+        gr = Groups(units * parts, (tiles + parts - 1) / parts);
+    }
+    DP_HD bool get(unsigned block, int& row, int& col, int& z) const
+    {
+        int g, t;
+        if (!gr.get(block, g, t)) return false;
+        const int unit = g / parts;
+        t += (g - unit * parts) * gr.size;
+        if (t >= tiles) return false;
+        const int r = t / tn;
+        col = t - r * tn;
+        row = split ? r : unit;
+        z = split ? unit : 0;
+        return true;
+    }
+};
+
 }  // namespace dp

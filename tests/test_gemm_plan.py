@@ -67,3 +67,38 @@ def test_every_tile_of_a_launch_is_one_block(tmp_path):
         if (n != (uint64_t)(s[0] * s[1])) { printf("%lld x %lld: %llu tiles\n", s[0], s[1], (unsigned long long)n); return 1; }
     }
     """)
+
+
+def test_every_tile_of_a_product_is_one_block(tmp_path):
+    """Row tiles from one to many, column tiles, split-K ranges; no XCD gets more than
+    its share of the groups (about 5 %, or one group where there are few tiles)."""
+    run(tmp_path, r"""
+    for (int tm : {1, 2, 3, 7, 8, 9, 31, 129, 1000})
+        for (int tn : {1, 2, 3, 5, 64, 625})
+            for (int z : {1, 2, 3, 13, 104}) {
+                if ((long long)tm * tn * z > 2000000) continue;
+                const TileMap map(tm, tn, z);
+                const Grid grid = gemm_grid(map.gr.blocks());
+                std::vector<bool> seen((size_t)tm * tn * z);
+                long long n = 0, xcd[8] = {};
+                for (uint64_t b = 0; b < (uint64_t)grid.x * grid.y; ++b) {
+                    int r, c, q;
+                    if (!map.get((unsigned)b, r, c, q)) continue;
+                    const long long at = ((long long)q * tm + r) * tn + c;
+                    if (r < 0 || r >= tm || c < 0 || c >= tn || q < 0 || q >= z || seen[at]) {
+                        printf("%d x %d x %d: block %llu\n", tm, tn, z, (unsigned long long)b);
+                        return 1;
+                    }
+                    seen[at] = true;
+                    ++n;
+                    ++xcd[b & 7];
+                }
+                long long most = 0;
+                for (long long x : xcd) most = x > most ? x : most;
+                const double fair = (double)n / 8;
+                if (n != (long long)tm * tn * z || most > 1.3 * fair + map.gr.size) {
+                    printf("%d x %d x %d: %lld tiles, %lld on an XCD\n", tm, tn, z, n, most);
+                    return 1;
+                }
+            }
+    """)
