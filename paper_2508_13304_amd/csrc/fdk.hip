@@ -10,8 +10,9 @@
 // The sums are FP64 (the ramp's cancellation between h[0] and the odd taps
 // would cost FP32 several digits on smooth rows).  Odd k couples the outputs
 // of one column parity with the inputs of the other, so rows of up to 2048
-// pixels are two Toeplitz products of half the size on the FP64 matrix cores;
-// longer ones take one block per row and two LDS reads per tap.
+// pixels are two Toeplitz products of half the size on the FP64 matrix cores, or
+// the same sums a row per block where there are few rows; longer ones take one
+// block per row and two LDS reads per pair of taps.
 //
 // Sharpness: S = -sum over x, y, z forward differences d of d^2 (pairs
 // inside the grid); dS/dmu_j = sum over axes of 2 (mu[j+e] - mu_j) where j+e
@@ -25,6 +26,8 @@
 // and GE in FP64; pass 2 writes dGE/dmu_i = sum over axes of
 // c_{i-e} d_{i-e} - c_i d_i with c_j = -(log g_j - log Z + GE) / (Z g_j),
 // recomputing g at i and at its three backward neighbours.
+#include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "dp_internal.h"
@@ -38,11 +41,15 @@ constexpr int kFdkMaxNu = 4000;  // LDS: 3 nu floats + nu/2 doubles <= 64 KiB
 // up to a tile of 16 and nuu up to 3 beyond the row.
 __host__ __device__ inline int fdk_table(int nu) { return nu + 32; }
 
+// Inputs of one parity, to a multiple of 4.
+__host__ __device__ inline int fdk_half(int nu) { return ((nu + 1) / 2 + 3) / 4 * 4; }
+
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float fdk_weighted(float p, double uu, double vv, double sad)
 {
-    return (float)((double)p * sad / sqrt(sad * sad + uu * uu + vv * vv));
+    // (explicit fma: the same rounding in every kernel)
+    return (float)((double)p * sad / sqrt(fma(vv, vv, fma(uu, uu, sad * sad))));
 }
 
 // 16 detector rows per block.  The 8 wavefronts share the tiles of 16 outputs
@@ -137,6 +144,67 @@ __global__ __launch_bounds__(64 * kFdkWaves) void fdk_filter_mfma_kernel(
     }
 }
 
+// One detector row per block, for launches of few rows: the same sums, in the same
+// order and hence to the same bits, on the vector units (the matrix instruction
+// adds its four products one fma after the other, in ascending k; padding adds
+// zeros).  A wavefront takes 64 neighbouring outputs of one parity, NJ times (nu <=
+// NJ threads), and walks the inputs of the other parity: per tap an FP64 table
+// read and fma, the inputs (as FP64 in LDS) are wave-uniform reads.
+template <int NJ>
+__global__ __launch_bounds__(1024) void fdk_filter_row_kernel(
+    int nu, int nv, double cu, double cv, double du_iso, double dv_iso, double sad, double tau,
+    double scale, const float* proj, float* out)  // proj == out allowed (row staged first)
+{
+    // in[e][n / 2]: the inputs n of parity e (zeros to a multiple of 4), then the table
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int half = fdk_half(nu), off = nu / 2 + 8, ntab = fdk_table(nu);
+    double* in = reinterpret_cast<double*>(smem);
+    double* h = in + 2 * half;
+    const int tid = threadIdx.x, threads = blockDim.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = blockIdx.x;  // row index over all views: v * nv + b
+    const float* src = proj + (size_t)r * nu;
+    const double vv = ((double)(r % nv) - cv) * dv_iso;
+    const double pi2tau2 = M_PI * M_PI * tau * tau, h0 = 1.0 / (4.0 * tau * tau);
+    for (int t = tid; t < ntab; t += threads) {
+        const double k = 2.0 * (t - off) + 1.0;
+        h[t] = -1.0 / (pi2tau2 * k * k);
+    }
+    for (int c = tid; c < 2 * half; c += threads)
+        in[(c & 1) * half + (c >> 1)] =
+            c < nu ? (double)fdk_weighted(src[c], ((double)c - cu) * du_iso, vv, sad) : 0.0;
+    __syncthreads();
+    const int e = wave & 1, n_out = (nu - e + 1) / 2, n_in = (nu + e) / 2;
+    const double* p = in + (1 - e) * half;
+    const double* own = in + e * half;
+    const int stride = threads / 2;  // outputs of a parity per round
+    double acc[NJ];
+    const double* hk[NJ];
+    int alpha[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        acc[j] = 0.0;
+        alpha[j] = (wave >> 1) * 64 + lane + j * stride;
+        hk[j] = h + (off + e - 1 + min(alpha[j], n_out - 1));
+    }
+    for (int c0 = 0; c0 < nu; c0 += kFdkChunk) {
+        const int k1 = min(n_in, (c0 + kFdkChunk) / 2);
+        for (int k = c0 / 2; k < k1; k += 4)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) acc[j] = fma(p[k + q], hk[j][-(k + q)], acc[j]);
+        // the chunk's own outputs: h[0] times their input
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (alpha[j] < n_out && alpha[j] >= c0 / 2 && alpha[j] < (c0 + kFdkChunk) / 2)
+                acc[j] = fma(h0, own[alpha[j]], acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+        if (alpha[j] < n_out) out[(size_t)r * nu + 2 * alpha[j] + e] = (float)(scale * tau * acc[j]);
+}
+
 __global__ __launch_bounds__(kFdkThreads) void fdk_filter_kernel(
     int nu, int nv, double cu, double cv, double du_iso, double dv_iso, double sad, double tau,
     double scale, const float* proj, float* out)  // proj == out allowed (row staged first)
@@ -178,6 +246,17 @@ __global__ __launch_bounds__(kFdkThreads) void fdk_filter_kernel(
     }
 }
 
+// Rows (of all views) from which the matrix kernel is faster: it takes 16 rows a
+// block, 8 wavefronts, so that a thousand rows are needed to fill the chip, and it
+// computes whole tiles of 128 outputs.  Kernel us, row by row against matrix: 512
+// pixels 16 rows 7.9 / 27.1, 600 20.9 / 28.0, 1200 32.3 / 28.5, 60000 1246 / 321;
+// 100 pixels 4800 rows 9.6 / 12.0, 20000 28.5 / 23.3; 2048 pixels 600 rows 222 / 297,
+// 1200 355 / 302; 16 pixels never.
+static int fdk_row_limit(int nu)
+{
+    return nu < 64 ? INT_MAX : nu <= 128 ? 8192 : nu <= 256 ? 1600 : nu <= 512 ? 1000 : nu <= 768 ? 900 : 700;
+}
+
 size_t fdk_filter_lds_bytes(int nu)
 {
     return sizeof(double) * (nu / 2 + 1) + sizeof(float) * 3 * (size_t)nu;
@@ -192,6 +271,14 @@ void launch_fdk_filter(const GeoScalars& s, int V, const float* proj, float* out
     // rows keep the direct kernel
     if (s.nu <= 2048) {
         const int rows = V * s.nv;
+        if (rows < fdk_row_limit(s.nu)) {
+            const int threads = std::min(1024, (s.nu + 127) / 128 * 128);
+            const size_t lds = sizeof(double) * (2 * fdk_half(s.nu) + fdk_table(s.nu));
+            const auto k = s.nu <= 1024 ? fdk_filter_row_kernel<1> : fdk_filter_row_kernel<2>;
+            k<<<(unsigned)rows, threads, lds, st>>>(s.nu, s.nv, s.cu, s.cv, du_iso, dv_iso, s.sad, du_iso, scale,
+                                                    proj, out);
+            return;
+        }
         const size_t lds = sizeof(float) * kFdkRows * kFdkPitch + sizeof(double) * fdk_table(s.nu);
         const auto k = s.nu <= 512 ? fdk_filter_mfma_kernel<4>
                                    : s.nu <= 1024 ? fdk_filter_mfma_kernel<8> : fdk_filter_mfma_kernel<16>;

@@ -39,3 +39,17 @@ def test_rows_do_not_mix(dp):
     # the ramp's even taps are zero: inf reaches its own pixel and the odd distances
     odd = (torch.arange(70) - 30) % 2 == 1
     assert torch.isfinite(got[0, 7, ~odd.cuda()]).sum() == 34 and not torch.isfinite(got[0, 7, odd.cuda()]).any()
+
+
+@pytest.mark.parametrize("nu,V", [(64, 95), (70, 95), (200, 20), (384, 12), (512, 12), (513, 11), (1025, 9), (2047, 8)])
+def test_a_view_does_not_depend_on_its_launch(dp, nu, V):
+    """Few rows take a kernel of their own: one view alone has the bits it has among
+    many, in place too."""
+    g = Geom(8, 8, 8, 1.0, 1.0, 1.0, nu, 90, 0.4, 0.5, off_u=0.75, off_v=-0.25)
+    x = torch.randn((V, 90, nu), generator=torch.Generator().manual_seed(nu)).cuda()
+    want = dp.fdk_filter(g, x, 0.1)
+    for v in (0, V - 1):
+        one = x[v:v + 1].clone()
+        assert torch.equal(dp.fdk_filter(g, one, 0.1)[0], want[v])
+        dp.fdk_filter(g, one, 0.1, out=one)
+        assert torch.equal(one[0], want[v])
