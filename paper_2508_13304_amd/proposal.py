@@ -347,6 +347,9 @@ class ProposalNet:
         """x: [N][H][W][2] BF16 (NHWC).  Returns FP32 [N][6] (and the cache)."""
         cache = []
         h = x.contiguous()
+        if (keep and h.shape[3] == 2 and h.data_ptr() == x.data_ptr()
+                and self._gathers(h, self.convs[0][0].shape[0])):
+            h = h.clone()  # backward gathers from it; the caller may have refilled x by then
         for li, (W, b, s) in enumerate(self.convs):
             K = W.shape[1]
             if h.shape[3] % 8 == 0:

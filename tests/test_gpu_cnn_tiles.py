@@ -124,3 +124,18 @@ def test_more_than_2_to_the_24_rows(dp):
     dx = pr.conv_dgrad_act(x, w, (1, h, 1, 8), 1)
     d = (dx[:, h - n:].double() - ref).abs() - (ref.abs() / 256 + 1e-5 * mag)
     assert (d[:, 2:] <= 0).all() and (dx[0, :h - n - 1] == 0).all()
+
+
+def test_input_refilled_between_forward_and_backward(dp):
+    from paper_2508_13304_amd import proposal as pr
+    net = pr.ProposalNet(size=32, channels=(32, 32), seed=4)
+    g = torch.Generator("cuda").manual_seed(2)
+    x = torch.randn((3, 32, 32, 2), device="cuda", generator=g).bfloat16()
+    dout = torch.randn((3, 6), device="cuda", generator=g)
+    _, cache = net.forward(x, keep=True)
+    net.backward(cache, dout)
+    want = net.G.clone()
+    _, cache = net.forward(x, keep=True)
+    x.zero_()
+    net.backward(cache, dout)
+    assert torch.equal(net.G, want)
