@@ -656,7 +656,10 @@ __device__ inline void load_box_interior(const Box& b, const float* __restrict__
 // to zero.  All loads of an item are issued before its stores: voxel by voxel
 // they were a chain of round trips to memory, which showed wherever few blocks
 // share a compute unit (forward of 256^3, one 384^2 view: 165 to 116 us;
-// gradient of 151x133x117, 12 views: 689 to 657).
+// gradient of 151x133x117, 12 views: 689 to 657).  Columns off the grid load
+// nothing: small volumes have many of them, and lost to the voxel-by-voxel
+// form with their loads (gradient of 33^3, 64 views of 50^2 871 to 945 us, 815
+// without; 64^3, 64 views of 128^2 2301 to 2267, 2090).
 template <int C>
 __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu, int nx, int ny,
                                      int nz, float* dst)
@@ -678,9 +681,11 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
         const auto on = [&](int k) { return col && (unsigned)k < (unsigned)nz; };
         unsigned slot = (unsigned)C * ((unsigned)z0 * (unsigned)b.pxy + (unsigned)ly * (unsigned)b.px + (unsigned)lx);
         if constexpr (C == 1) {
-            float v[SEG];
+            float v[SEG] = {};
+            if (col) {
 #pragma unroll
-            for (int q = 0; q < SEG; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
+                for (int q = 0; q < SEG; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
+            }
 #pragma unroll
             for (int q = 0; q < SEG; ++q, slot += dslot)
                 if (q < cnt) box_store<C>(dst, slot, on(k0 + q) ? v[q] : 0.f, 0.f, 0.f, 0.f);
@@ -688,16 +693,18 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
             const bool fxm = i > 0, fxp = i + 1 < nx, fym = j > 0, fyp = j + 1 < ny;
             const unsigned oxm = oc - (col && fxm ? 4u : 0u), oxp = oc + (col && fxp ? 4u : 0u);
             const unsigned oym = oc - (col && fym ? nx4 : 0u), oyp = oc + (col && fyp ? nx4 : 0u);
-            float c[SEG + 2], w[SEG][4];
+            float c[SEG + 2] = {}, w[SEG][4] = {};
+            if (col) {
 #pragma unroll
-            for (int q = 0; q < SEG + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
+                for (int q = 0; q < SEG + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
 #pragma unroll
-            for (int q = 0; q < SEG; ++q) {
-                const unsigned o = plane(k0 + q);
-                w[q][0] = ldv(mu, o + oxm);
-                w[q][1] = ldv(mu, o + oxp);
-                w[q][2] = ldv(mu, o + oym);
-                w[q][3] = ldv(mu, o + oyp);
+                for (int q = 0; q < SEG; ++q) {
+                    const unsigned o = plane(k0 + q);
+                    w[q][0] = ldv(mu, o + oxm);
+                    w[q][1] = ldv(mu, o + oxp);
+                    w[q][2] = ldv(mu, o + oym);
+                    w[q][3] = ldv(mu, o + oyp);
+                }
             }
 #pragma unroll
             for (int q = 0; q < SEG; ++q, slot += dslot) {
