@@ -266,9 +266,17 @@ inline int rd_tiles(const GeoScalars& s, int shape)
 // 1 view 63 / 26, 16 views 108 / 104, 100 views 586 / 610; 144 tiles (96^3,
 // 192^2) 1 view 70 / 32, 8 views 144 / 119; 256 tiles (128^3, 256^2) 1 view
 // 68 / 39, 8 views 176 / 183, 100 views 2235 / 2531; 1024 tiles (320^3, 512^2,
-// 16 views) 1995 / 2820.  Chunks of 64 samples in the middle class's box array
-// (eight blocks on a compute unit): 32 samples take 34 us at 64 tiles.
-constexpr int kRdSplitTiles = 144, kRdSplitM = 64, kRdSplitCap = 5064;
+// 16 views) 1995 / 2820.  The price is paid by many views whose rays lie much
+// closer than the voxels, which share their boxes best in large tiles: at less
+// than 0.4 voxels apart (at the isocentre) and 65 to 144 tiles, 1 view takes 0.48
+// of the time whole, 4 views 0.7, 16 views 0.95, 64 views 1.1 to 1.2; from 0.4 to 1
+// voxel apart 64 views take at most 1.13, on average 0.75.
+// Chunks of 64 samples in the middle class's box array (eight blocks on a
+// compute unit): 32 samples take 34 us at 64 tiles.  Chunks of less than 5 samples
+// are not staged: where rays lie two voxels and more apart they cost more than the
+// taps themselves (16 views of 50^2 from 64^3, tilted: 614 us, 211 without; 1 view
+// of 128^2 from 200^3 515 and 107).
+constexpr int kRdSplitTiles = 144, kRdSplitM = 64, kRdSplitMin = 5, kRdSplitCap = 5064;
 __host__ __device__ inline bool rd_fwd_split(const GeoScalars& s, int variant)
 {
     return variant == kRdDefaultVariant &&

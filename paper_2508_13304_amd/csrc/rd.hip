@@ -283,7 +283,7 @@ __device__ inline Box chunk_box(const TileShared& sh, int K, int Ke, float step,
 }
 
 // The chunk length M for which all boxes of the tile fit `cap` voxels, or 0
-// if none does (the tile then reads its taps from global memory).  M shrinks
+// if none of at least MMIN does (the tile then reads its taps from global memory).  M shrinks
 // in steps of max(2, M / 8) (16 -> 14 -> 12 ...): a tile whose widest box
 // overflows by a few percent keeps most of its chunk length.  The wavefronts
 // try four successive lengths at a time, a lane per chunk, and the first that
@@ -292,7 +292,7 @@ __device__ inline Box chunk_box(const TileShared& sh, int K, int Ke, float step,
 // orbit views: 3.69 to 3.62 ms with it; single-pass SSD of 256^3, 64 views:
 // 13.94 to 13.77).
 // Thread i < the chunk count leaves the record of chunk i in `rec`.
-template <int C>
+template <int C, int MMIN = 1>
 __device__ inline int plan_chunks(TileShared& sh, int Kmin, int Kmax, int Mmax, int cap,
                                   float step, float margin, int NX, int NY, int NZ, BoxRec& rec)
 {
@@ -315,8 +315,8 @@ __device__ inline int plan_chunks(TileShared& sh, int Kmin, int Kmax, int Mmax, 
                        (float)slice_pitch<C>(px, b.by) * (float)b.bz > (float)cap;
             }
         // fits: the length; shorten further: -1; no length will do: 0
-        const bool fits = nch <= kMaxChunks && __builtin_amdgcn_ballot_w64(over) == 0;
-        if (lane == 0) sh.vmax[wave] = fits ? Mw : nch > kMaxChunks || Mw == 1 ? 0 : -1;
+        const bool fits = nch <= kMaxChunks && Mw >= MMIN && __builtin_amdgcn_ballot_w64(over) == 0;
+        if (lane == 0) sh.vmax[wave] = fits ? Mw : nch > kMaxChunks || Mw <= MMIN ? 0 : -1;
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 4 && !found; ++q) {
@@ -859,12 +859,12 @@ __device__ inline void fwd_samples(const float* lds, const Box& bx, const ChunkR
 // Sum of the samples klo .. khi of one ray straight from the volume (a tile
 // whose chunk boxes are too large for LDS).
 __device__ inline float fwd_samples_global(const GeoScalars& s, const RayState& r, const float* __restrict__ mu,
-                                           int klo, int khi)
+                                           int klo, int khi, int stride = 1)
 {
     const float xmax = s.nx + 2 * kPadV - 1.001f, ymax = s.ny + 2 * kPadV - 1.001f,
                 zmax = s.nz + 2 * kPadV - 1.001f, step = (float)s.step;
     float acc = 0.0f;
-    for (int k = klo; k <= khi; ++k) {
+    for (int k = klo; k <= khi; k += stride) {
         const float t = fmaf((float)(k - r.k0), step, r.f);
         const float X = fminf(fmaxf(fmaf(t, r.dx, r.x0), 0.0f), xmax);
         const float Y = fminf(fmaxf(fmaf(t, r.dy, r.y0), 0.0f), ymax);
@@ -928,7 +928,7 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
     const int klo = active ? r.klo : 1, khi = active ? r.khi : 0;
     float acc = 0.0f;
     BoxRec rec = {};
-    const int M = Kmin <= Kmax ? plan_chunks<1>(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
+    const int M = Kmin <= Kmax ? plan_chunks<1, SPLIT ? kRdSplitMin : 2>(sh, Kmin, Kmax, MCH, CAP, step, margin, NX, NY, NZ,
                                              rec)
                                : 1;
     if (M > 0) {
@@ -946,8 +946,9 @@ __device__ inline void rd_fwd_tile(const GeoScalars& s, const ViewGeo* __restric
             fwd_samples<CAP>(lds, bx, chunk_ray(r, kb, ke, bx, step), acc);
         }
     } else if (SPLIT) {
-        const int q = (Kmax - Kmin) / 4 + 1, Kw = Kmin + wave * q;
-        acc = fwd_samples_global(s, r, mu, max(klo, Kw), min(khi, Kw + q - 1));
+        // every fourth sample: the wavefronts keep to one depth, whose voxels they share
+        // (16 views of 128^2 from 320^3: 3.01 ms in quarters of the range, 1.92 so)
+        acc = fwd_samples_global(s, r, mu, klo + wave, khi, 4);
     } else {
         acc = fwd_samples_global(s, r, mu, klo, khi);
     }

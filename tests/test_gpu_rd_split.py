@@ -66,3 +66,29 @@ def test_a_view_does_not_depend_on_its_launch(dp):
     every = project(dp, g, vol, angles, poses)
     for i in (0, 4, 8):
         assert np.array_equal(project(dp, g, vol, angles[i:i + 1], poses[i:i + 1])[0], every[i])
+
+
+# rays far apart, whose chunks are not worth staging (every fourth sample per
+# wavefront straight from the volume), split and whole; rays close together
+SPACINGS = [((100, 97, 95), 1.5, 50, 47, 6.6, 3), ((160, 150, 140), 0.9, 100, 97, 3.0, 2),
+            ((160, 150, 140), 0.9, 200, 190, 3.0, 2), ((33, 30, 28), 4.5, 160, 157, 1.2, 2)]
+
+
+@pytest.mark.parametrize("n,h,nu,nv,du,V", SPACINGS)
+def test_ray_spacings(dp, oracle, n, h, nu, nv, du, V):
+    test_small_launches(dp, oracle, n, h, nu, nv, du, V)
+
+
+def test_batches_of_ray_spacings(dp):
+    rng = synth.rng_for(1300)
+    prs, want = [], []
+    for n, h, nu, nv, du, V in SPACINGS:
+        g = Geom(*n, h, h, h, nu, nv, du, du)
+        t = [torch.tensor(np.ascontiguousarray(a), dtype=d, device="cuda:0")
+             for a, d in ((rng.uniform(0, 2 * math.pi, V), torch.float64), (synth.random_poses(V, 2.0, 9.0, rng), torch.float64),
+                          (rng.uniform(0, 0.05, g.vol_shape), torch.float32))]
+        want.append(dp.project_fwd(g, *t))
+        prs.append(dict(geom=g, angles=t[0], poses=t[1], vol=t[2], proj=torch.zeros_like(want[-1])))
+    dp.project_fwd_batch(prs, variant=1)
+    for p, w in zip(prs, want):
+        assert torch.equal(p["proj"], w)
