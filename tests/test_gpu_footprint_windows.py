@@ -96,3 +96,28 @@ def test_voxel_without_a_number_reaches_its_pixels_only(dp, oracle, name, kind, 
     ok = away & ~rim
     # (FP32 atomics: the last bits depend on the order of the sums)
     assert np.abs(got[ok] - clean[ok]).max() <= 1e-5 * np.abs(clean).max()
+
+
+# blocks that take several views each: 100 blocks (20 share the views of a brick, so
+# that 47 views make two or three a block) and 2048 (every block takes them all)
+@pytest.mark.parametrize("n,V", [((70, 40, 40), 47), ((64, 256, 256), 3)])
+@pytest.mark.parametrize("kind", ["sf", "dd"])
+def test_gradient_of_a_view_does_not_depend_on_its_launch(dp, oracle, kind, n, V):
+    g = Geom(*n, 1.0, 1.0, 1.0, 61, 49, 2.0, 2.0, off_u=1.5)
+    rng = synth.rng_for(795)
+    angles, poses = rng.uniform(0, 2 * math.pi, V), synth.random_poses(V, 2.0, 9.0, rng)
+    vol, e = f32(rng.uniform(0.0, 0.05, g.vol_shape).astype(np.float32)), f32(rng.standard_normal(g.vol_shape).astype(np.float32))
+    img = f32(rng.standard_normal((V, g.nv, g.nu)).astype(np.float32))
+    a, p = f64(angles), f64(poses)
+    fwd = dp.fp_project_grad_pose(g, a, p, vol, img, kind).cpu().numpy()
+    back = dp.fp_backproject_grad_pose(g, a, p, img, e, kind).cpu().numpy()
+    for v in range(V):
+        one = slice(v, v + 1)
+        np.testing.assert_array_equal(dp.fp_project_grad_pose(g, a[one], p[one], vol, img[one], kind).cpu().numpy(), fwd[one])
+        np.testing.assert_array_equal(dp.fp_backproject_grad_pose(g, a[one], p[one], img[one], e, kind).cpu().numpy(), back[one])
+    last = slice(V - 1, V)
+    if n[0] == 70:
+        check_grads(f"{kind} project_grad_pose", fwd[last],
+                    oracle.fp_project_grad_pose(g, angles[last], poses[last], vol.cpu().numpy(), img[last].cpu().numpy(), kind))
+        check_grads(f"{kind} backproject_grad_pose", back[last],
+                    oracle.fp_backproject_grad_pose(g, angles[last], poses[last], img[last].cpu().numpy(), e.cpu().numpy(), kind))
