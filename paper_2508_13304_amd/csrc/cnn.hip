@@ -16,8 +16,8 @@
 //   dx   = col2im(dcol)         gather of the overlapping windows.
 //
 // GEMM: C[M][N] (FP32) = op(A) op(B) (+ C if accumulate), A/B BF16.  A block
-// computes a 128x128, 128x64 or 64x64 tile with 2 x 2 wavefronts (MFMA
-// 16x16x32 tiles); K advances by 64 through LDS.  Operand lane layout of
+// computes a 128x128, 128x64 or 64x64 tile with 2 x 2 wavefronts, or a 128x32 or
+// 64x32 one with 4 x 1 (MFMA 16x16x32 tiles); K advances by 64 through LDS.  Operand lane layout of
 // v_mfma_f32_16x16x32_bf16: lane l supplies row (l % 16) of A and column
 // (l % 16) of B, each with the 8 consecutive k = 8 (l / 16) .. +7; it receives
 // D rows 4 (l / 16) .. +3 of column (l % 16).
@@ -232,8 +232,7 @@ struct Im2colA {
 struct Im2colB {
     static constexpr bool KC = false, kGuarded = false;
     const __bf16* x;
-    ConvGeo g;
-    int ncols;  // columns of the product (row length of dW)
+    ConvGeo g;  // (columns past the product's are zero and not stored)
     template <int R>
     struct St { int dy, dx; unsigned ci, fill; bool tap; };
     template <int R>
@@ -916,7 +915,7 @@ void launch_conv_wgrad(int N, int H, int W, int Ci, int Co, int s, const void* x
 {
     const ConvGeo g = conv_geo(N, H, W, Ci, s, ones);
     run_gemm_f32(Co, ldw, g.M, DenseSrc<false, kWhole>{(const __bf16*)dz, Co, Co},
-                 Im2colB{(const __bf16*)x, g, ldw}, dw, ldw, false, ws, ws_bytes, st);
+                 Im2colB{(const __bf16*)x, g}, dw, ldw, false, ws, ws_bytes, st);
 }
 
 void launch_conv2_fwd(int N, int H, int W, int Co, int s, const void* x, const void* w, int ldw,

@@ -200,14 +200,14 @@ void launch_conv_fwd(int N, int H, int W, int Ci, int Co, int s, const void* x, 
 size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co, int s, int ldw);
 void launch_conv_wgrad(int N, int H, int W, int Ci, int Co, int s, const void* x, const void* dz,
                        int ldw, bool ones, float* dw, float* ws, size_t ws_bytes, hipStream_t st);
-// Input gradient, per parity class of input pixels, with the ReLU backward
-// of the layer below: out [N][H][W][Ci] BF16 = dx (y == NULL or !relu) or
-// dx * (y > 0).
-// The same for a two-channel input (Co a multiple of 32; dw with the ones column)
+// Both for a two-channel input (Co a multiple of 32; dw with the ones column)
 void launch_conv2_fwd(int N, int H, int W, int Co, int s, const void* x, const void* w, int ldw,
                       const float* bias, int bias_stride, bool relu, void* y, hipStream_t st);
 void launch_conv2_wgrad(int N, int H, int W, int Co, int s, const void* x, const void* dz, int ldw,
                         float* dw, float* ws, size_t ws_bytes, hipStream_t st);
+// Input gradient, per parity class of input pixels, with the ReLU backward
+// of the layer below: out [N][H][W][Ci] BF16 = dx (y == NULL or !relu) or
+// dx * (y > 0).
 void launch_conv_dgrad_act(int N, int H, int W, int Ci, int Co, int s, const void* dz,
                            const void* w, int ldw, const void* y, bool relu, void* out,
                            hipStream_t st);

@@ -27,8 +27,10 @@
 // axis-aligned bounding box is loaded once, coalesced, into LDS and every
 // trilinear tap is an LDS read.  All chunk boxes of a tile are planned up
 // front, one per thread; M shrinks in steps until every box fits the LDS
-// budget, and a tile whose boxes do not fit even at M = 1 (or need more
-// chunks than threads) reads its taps from global memory.
+// budget, and a tile whose boxes do not fit even at M = 1 (forward: 2), or need
+// more chunks than threads, reads its taps from global memory.  The forward on a
+// small detector takes tiles of 8x8 pixels instead, one ray per lane of each of
+// the four wavefronts, which share the samples of every chunk (M of 5 or more).
 //
 // Numerics: per-ray setup in FP64; each ray is anchored at its crossing of
 // the iso-plane (a point of small magnitude) and, per chunk, re-anchored at

@@ -811,16 +811,18 @@ __device__ inline void sf_scatter(const SfColumn& c, const GeoScalars& s, int do
 }
 
 template <int KIND>
-__global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_fwd_kernel(GeoScalars s, int steps, int cap,
+__global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_fwd_kernel(GeoScalars s, int steps,
                                                                   const ViewGeo* __restrict__ views,
                                                                   const float* __restrict__ vol,
                                                                   float* __restrict__ proj)
 {
-    extern __shared__ float tiles[];  // per wavefront cap pixels and a dump for 3 x 4 more
+    // per wavefront a tile, then a dump for the four columns of a row outside it
+    // (of static size it costs four to five more spilled registers)
+    extern __shared__ float tiles[];
     const ViewGeo& g = views[blockIdx.y];
     float* img = proj + (size_t)blockIdx.y * s.nu * s.nv;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.y), lane = threadIdx.x;
-    float* tile = tiles + wave * (cap + kSfPatchCols);
+    float* tile = tiles + wave * (kSfTile + kSfPatchCols);
     double src[3];
     const int dom = __builtin_amdgcn_readfirstlane(sf_source(g, s, src));
     // across: the lanes' axis, along: the other one
@@ -841,12 +843,12 @@ __global__ __launch_bounds__(kSfBx * kSfBy, 4) void sf_fwd_kernel(GeoScalars s, 
         for (;; sub = (sub + 1) / 2) {
             const int ka = kb + k0, ke = min(ka + sub, kb + nk) - 1;
             rect = dom == 0 ? sf_rect(g, s, q0, q1, p0, p1, ka, ke) : sf_rect(g, s, p0, p1, q0, q1, ka, ke);
-            if (!rect.known || rect.w * rect.h <= cap || sub == 1) break;
+            if (!rect.known || rect.w * rect.h <= kSfTile || sub == 1) break;
         }
         const int ke = min(sub, nk - k0);
         const int npix = rect.w * rect.h;
         if (rect.known && npix == 0) continue;  // no footprint of these voxels reaches the detector
-        const bool tiled = rect.known && npix <= cap && s.nu >= 4;
+        const bool tiled = rect.known && npix <= kSfTile && s.nu >= 4;
         if (tiled)
             for (int t = lane; t < npix; t += 64) tile[t] = 0.0f;
         for (int q = q0; q <= q1; ++q) {
@@ -1150,12 +1152,11 @@ void launch_sf_fwd(const GeoScalars& s, int V, const ViewGeo* views, const float
     int steps = kSfSteps;
     while (steps > 1 && (long long)bricks(steps) * V * zb < kSfFwdWaves) steps /= 2;
     const dim3 grid((bricks(steps) + kSfBy - 1) / kSfBy, V, zb), block(kSfBx, kSfBy);
-    const int cap = kSfTile;
-    const size_t lds = kSfBy * (cap + kSfPatchCols) * sizeof(float);
+    constexpr size_t lds = kSfBy * (kSfTile + kSfPatchCols) * sizeof(float);
     prof_begin(DP_K_SF, st);
     sf_zero_kernel<<<fill, 256, 0, st>>>(n, proj);
-    if (kind == kFpDD) sf_fwd_kernel<kFpDD><<<grid, block, lds, st>>>(s, steps, cap, views, vol, proj);
-    else sf_fwd_kernel<kFpSF><<<grid, block, lds, st>>>(s, steps, cap, views, vol, proj);
+    if (kind == kFpDD) sf_fwd_kernel<kFpDD><<<grid, block, lds, st>>>(s, steps, views, vol, proj);
+    else sf_fwd_kernel<kFpSF><<<grid, block, lds, st>>>(s, steps, views, vol, proj);
     prof_end(DP_K_SF, st);
 }
 
