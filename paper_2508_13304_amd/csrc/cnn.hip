@@ -185,6 +185,10 @@ struct ConvGeo {
     FastDiv hw, w, c;            // by Ho Wo, Wo, C
 };
 
+// A row offset that takes every row (fewer than 2^28: at least 8 channels, 2^31
+// elements) out of the image: chunks beyond the reduction.
+constexpr int kNoRow = -(1 << 30);
+
 // The im2col matrix of the input x as the GEMM's A (rows = output pixels,
 // KC): a thread keeps its rows' first tap, and per step the tap of its k.
 struct Im2colA {
@@ -214,13 +218,12 @@ struct Im2colA {
     {
         const unsigned k = (unsigned)(k0 + Chunk<true, R>::k(tid, 0));  // the chunks' common k
         const unsigned t = g.c.div(k);
-        const int ky = (int)t / 3, kx = (int)t - 3 * ky;
-        const bool some = (int)k < kend;
+        const int ky = (int)k < kend ? (int)t / 3 : kNoRow, kx = (int)t - 3 * ((int)t / 3);
         const unsigned tap = 2u * (((t / 3) * (unsigned)g.W + (unsigned)kx) * (unsigned)g.C + (k - t * (unsigned)g.C));
         const __amdgpu_buffer_rsrc_t r = tile_rsrc(x);
 #pragma unroll
         for (int u = 0; u < R / 32; ++u) {
-            const bool in = some && (unsigned)(st.y[u] + ky) < (unsigned)g.H && (unsigned)(st.x[u] + kx) < (unsigned)g.W;
+            const bool in = (unsigned)(st.y[u] + ky) < (unsigned)g.H && (unsigned)(st.x[u] + kx) < (unsigned)g.W;
             o[u] = load8(r, in ? st.off[u] + tap : kOut);
         }
     }
@@ -340,7 +343,7 @@ struct DgradA {
             const unsigned n = c.hw.div((unsigned)m), r = (unsigned)m - n * (unsigned)(c.Hc * c.Wc);
             const unsigned yc = c.w.div(r), xc = r - yc * (unsigned)c.Wc;
             st.off[u] = 2u * (((n * (unsigned)g.Ho + yc) * (unsigned)g.Wo + xc) * (unsigned)g.Co);
-            st.y[u] = m < c.M ? (int)yc : -2;  // (dy is at most 1)
+            st.y[u] = m < c.M ? (int)yc : kNoRow / 2;
             st.x[u] = (int)xc;
         }
         return st;
@@ -350,14 +353,13 @@ struct DgradA {
     {
         const unsigned k = (unsigned)(k0 + Chunk<true, R>::k(tid, 0));
         const unsigned t = g.co.div(k), ty = c.nkxd.div(t), tx = t - ty * (unsigned)c.nkx;
-        const int dy = c.dy0 - (int)ty, dx = c.dx0 - (int)tx;
-        const bool some = (int)k < kend;
-        const unsigned tap = 2u * (((unsigned)dy * (unsigned)g.Wo + (unsigned)dx) * (unsigned)g.Co +
+        const int dy = (int)k < kend ? c.dy0 - (int)ty : kNoRow, dx = c.dx0 - (int)tx;
+        const unsigned tap = 2u * (((unsigned)(c.dy0 - (int)ty) * (unsigned)g.Wo + (unsigned)dx) * (unsigned)g.Co +
                                    (k - t * (unsigned)g.Co));
         const __amdgpu_buffer_rsrc_t r = tile_rsrc(dz);
 #pragma unroll
         for (int u = 0; u < R / 32; ++u) {
-            const bool in = some && (unsigned)(st.y[u] + dy) < (unsigned)g.Ho && (unsigned)(st.x[u] + dx) < (unsigned)g.Wo;
+            const bool in = (unsigned)(st.y[u] + dy) < (unsigned)g.Ho && (unsigned)(st.x[u] + dx) < (unsigned)g.Wo;
             o[u] = load8(r, in ? st.off[u] + tap : kOut);
         }
     }

@@ -69,32 +69,36 @@ inline Grid gemm_grid(uint64_t blocks)
 // 5 in parts.
 struct TileMap {
     Groups gr;
-    int parts, tn, tiles;  // tiles of an undivided group
+    int lg, tn, tiles;  // log2 of the parts; tiles of an undivided group
     bool split;
-    static int parts_of(int units, int tiles)
+    static int log2_parts(int units, int tiles)
     {
-        int p = 1;
-        while (p < tiles && (units * (int64_t)p + 7) / 8 * 8 > 1.05 * units * (double)p) p *= 2;
-        return p;
+        int l = 0;
+        while (1 << l < tiles && (((int64_t)units << l) + 7) / 8 * 8 > 1.05 * (double)((int64_t)units << l)) ++l;
+        return l;
     }
     TileMap(int tm, int tn_, int z)
-        : gr(1, 1), parts(1), tn(tn_), tiles(z > 1 ? tm * tn_ : tn_), split(z > 1)
+        : gr(1, 1), lg(0), tn(tn_), tiles(z > 1 ? tm * tn_ : tn_), split(z > 1)
     {
         const int units = z > 1 ? z : tm;
-        parts = parts_of(units, tiles);
-        gr = Groups(units * parts, (tiles + parts - 1) / parts);
+        lg = log2_parts(units, tiles);
+        gr = Groups(units << lg, (tiles + (1 << lg) - 1) >> lg);
     }
     DP_HD bool get(unsigned block, int& row, int& col, int& z) const
     {
         int g, t;
         if (!gr.get(block, g, t)) return false;
-        const int unit = g / parts;
-        t += (g - unit * parts) * gr.size;
+        const int unit = g >> lg;
+        t += (g - (unit << lg)) * gr.size;
         if (t >= tiles) return false;
-        const int r = t / tn;
-        col = t - r * tn;
-        row = split ? r : unit;
-        z = split ? unit : 0;
+        row = unit;
+        col = t;
+        z = 0;
+        if (split) {
+            z = unit;
+            row = t / tn;
+            col = t - row * tn;
+        }
         return true;
     }
 };
