@@ -178,11 +178,13 @@ __device__ inline int lds_pitch(int n) { return n | 1; }
 // wavefront's 8x8 rays sample, as a rule, 8 neighbours along a row, or down
 // the rows, of 8 neighbouring slices.  The odd row pitch spreads either run
 // over 8 banks, and a slice pitch of 8 modulo 16 sets the eight runs side by
-// side over all 64, where an odd one overlaps them: 192^3, 100 views 2695 to
-// 2157 us (random angles 3596 to 2930), 256^3, 16 views 955 to 754; few tiles
-// gain nothing and lose nothing.  The gradient's 16-byte voxels are read a
-// quarter wavefront at a time and lose with it (single-pass SSD of 256^3, 64
-// views 13.6 to 14.6 ms; 2, 4, 6 and 12 modulo 16: 13.65 to 15.1).
+// side over all 64, where an odd one overlaps them.  Kernel us, odd against this:
+// 192^3, 100 views of 256^2 within 10 mm and 10 degrees of one view 2680 / 2150,
+// within 30 mm and 20 degrees 2883 / 2664, around the orbit 3600 / 2900; 256^3, 16
+// views of 384^2 958 / 772; rays half a voxel apart lose 2 % (256^3, 64 views of
+// 512^2: 4440 / 4547, LDS conflict cycles 14 against 18 %).  The gradient's 16-byte
+// voxels are read a quarter wavefront at a time and lose with it (single-pass SSD of
+// 256^3, 64 views 13.6 to 14.6 ms; 2, 4, 6 and 12 modulo 16: 13.65 to 15.1).
 template <int C>
 __device__ inline int slice_pitch(int px, int by)
 {
@@ -1421,9 +1423,10 @@ __global__ __launch_bounds__(kRdThreads, 4) void rd_fused_batch_kernel(RdBatch b
 
 // Chunk classes (chunk length before adaptation, LDS voxels) per kernel kind:
 //   forward : (16, 4096) (32, 5064) (64, 12288)  (middle class: 20,456 bytes, the most of
-//             which eight blocks fit a compute unit; kernel us at 4928, 5064, 5790, 6760:
-//             192^3, 100 views of random poses 2787, 2547, 2508, 2531, around the orbit
-//             3385, 3346, 3385, 3266; 256^3, 64 views of 512^2 4316, 4379, 4443, 4704)
+//             which eight blocks fit a compute unit; kernel us at 4928, 5064, 5790, 6760
+//             voxels: 192^3, 100 views of 256^2 within 10 mm and 10 degrees 2182, 2150, 2155,
+//             2252, within 30 mm and 20 degrees 2961, 2664, 2464, 2484, around the orbit
+//             2925, 2900, 2874, 2743; 256^3, 64 views of 512^2 4573, 4547, 4681, 4881)
 //   gradient: ( 8, 2048) (16, 2520) (32, 4096)
 //   fused   : ( 8, 2048) (16, 2520) (32, 4096)  (both: four channels per voxel)
 // The fused and gradient kernels' first two classes take at most 40,520

@@ -431,7 +431,9 @@ __device__ inline void sf_for_each(const SfFootprint& f, Fn&& fn)
 // pixels, against loops over each lane's own window in an unrolled column:
 // DD back-projection of 64 views 9.88 -> 3.79 ms (2.8e11 voxel-view updates/s,
 // about 110 VALU instructions each beside the FP64 column anchors) and its
-// gradient 5.40 -> 2.18 ms; SF forward gradient of 4 views 0.78 -> 0.30 ms.
+// gradient 5.40 -> 2.18 ms; SF forward gradient of 4 views 0.78 -> 0.30 ms.  VALU
+// busy 130, 47 and 97 % of the 4-cycle model (the back-projection gradient's
+// volume is mostly zero there), texture addresser 55, 27 and 34 %.
 // Four blocks per CU; five or six spill and are slower (1.03x, 1.4x).
 // ---------------------------------------------------------------------------
 
@@ -667,7 +669,9 @@ __device__ inline void sf_walk(const SfColumn& col, const ViewGeo& g, const GeoS
 // Voxels with wider windows, and those that hold no number, go to memory pixel by pixel.
 // FP32 atomics are what this avoids: straight to memory, one per pixel of
 // every footprint, they took most of the kernel's time, and LDS ones take
-// about 110 cycles per wavefront (measured: ds_add_f32, no conflicts).
+// about 110 cycles per wavefront (measured: ds_add_f32, no conflicts).  What is
+// left is the chain of each column's read, add and write: VALU busy 53 % of the
+// 4-cycle model, texture addresser 34 %, LDS conflicts 2 % of cycles.
 // ---------------------------------------------------------------------------
 
 // Voxels along the rays per brick, and tile pixels per wavefront (four blocks,

@@ -585,6 +585,9 @@ struct StageRect {
 // image lies in the hull of theirs), window-clamped like the voxels, plus a
 // safety margin.  Wavefront 0 computes it; w = 0 unless every corner lies at
 // least 1 mm in front of the source and the rectangle fits kVgStage pixels.
+// 512^3 of 0.375 mm stages every block (600 pixels at most; texture addresser
+// 10 % busy, 8.6e11 updates/s); 256^3 of 0.75 mm, 1.45 pixels a voxel, projects a
+// block onto more than 1000 pixels and gathers (77 %, 5.0e11).
 __device__ inline void stage_rect(const ViewGeo& g, const GeoScalars& s, int kb, int K,
                                   StageRect& out)
 {
