@@ -661,9 +661,10 @@ __device__ inline void load_box_interior(const Box& b, const float* __restrict__
 // they were a chain of round trips to memory, which showed wherever few blocks
 // share a compute unit (forward of 256^3, one 384^2 view: 165 to 116 us;
 // gradient of 151x133x117, 12 views: 689 to 657).  Columns off the grid load
-// nothing: small volumes have many of them, and lost to the voxel-by-voxel
-// form with their loads (gradient of 33^3, 64 views of 50^2 871 to 945 us, 815
-// without; 64^3, 64 views of 128^2 2301 to 2267, 2090).
+// nothing, nor do the upper halves of items where a wavefront has only short
+// ones: small volumes have many of both, and lost to the voxel-by-voxel form
+// with their loads (gradient of 33^3, 64 views of 50^2 880 to 957 us, 830 without;
+// 64^3, 64 views of 128^2 2.31 to 2.44 ms, 2.36; one 200^2 view 123 to 124 us, 121).
 template <int C>
 __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu, int nx, int ny,
                                      int nz, float* dst)
@@ -683,12 +684,16 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
         const unsigned oc = ((unsigned)min(max(j, 0), ny - 1) * (unsigned)nx + (unsigned)min(max(i, 0), nx - 1)) * 4u;
         const auto plane = [&](int k) { return (unsigned)min(max(k, 0), nz - 1) * nxy4; };
         const auto on = [&](int k) { return col && (unsigned)k < (unsigned)nz; };
+        const bool deep = __builtin_amdgcn_ballot_w64(cnt > SEG / 2) != 0;  // any item of this wavefront
         unsigned slot = (unsigned)C * ((unsigned)z0 * (unsigned)b.pxy + (unsigned)ly * (unsigned)b.px + (unsigned)lx);
         if constexpr (C == 1) {
             float v[SEG] = {};
             if (col) {
 #pragma unroll
-                for (int q = 0; q < SEG; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
+                for (int q = 0; q < SEG / 2; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
+                if (deep)
+#pragma unroll
+                    for (int q = SEG / 2; q < SEG; ++q) v[q] = ldv(mu, plane(k0 + q) + oc);
             }
 #pragma unroll
             for (int q = 0; q < SEG; ++q, slot += dslot)
@@ -698,16 +703,23 @@ __device__ inline void load_box_edge(const Box& b, const float* __restrict__ mu,
             const unsigned oxm = oc - (col && fxm ? 4u : 0u), oxp = oc + (col && fxp ? 4u : 0u);
             const unsigned oym = oc - (col && fym ? nx4 : 0u), oyp = oc + (col && fyp ? nx4 : 0u);
             float c[SEG + 2] = {}, w[SEG][4] = {};
+            const auto around = [&](int q) {
+                const unsigned o = plane(k0 + q);
+                w[q][0] = ldv(mu, o + oxm);
+                w[q][1] = ldv(mu, o + oxp);
+                w[q][2] = ldv(mu, o + oym);
+                w[q][3] = ldv(mu, o + oyp);
+            };
             if (col) {
 #pragma unroll
-                for (int q = 0; q < SEG + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
+                for (int q = 0; q < SEG / 2 + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
 #pragma unroll
-                for (int q = 0; q < SEG; ++q) {
-                    const unsigned o = plane(k0 + q);
-                    w[q][0] = ldv(mu, o + oxm);
-                    w[q][1] = ldv(mu, o + oxp);
-                    w[q][2] = ldv(mu, o + oym);
-                    w[q][3] = ldv(mu, o + oyp);
+                for (int q = 0; q < SEG / 2; ++q) around(q);
+                if (deep) {
+#pragma unroll
+                    for (int q = SEG / 2 + 2; q < SEG + 2; ++q) c[q] = ldv(mu, plane(k0 + q - 1) + oc);
+#pragma unroll
+                    for (int q = SEG / 2; q < SEG; ++q) around(q);
                 }
             }
 #pragma unroll
